@@ -6,18 +6,19 @@ Bg=2^7 l=3, key switch base 2^2 t=8 (the default parameter set).  A step is
 one cggi_eval_level call over that level: linear pre-op, modulus switch,
 accumulator init, 630 CMux steps, sample extraction and key switch for every
 gate, writing the 1024 output wires.  Inputs and keys are resident in HBM
-before timing starts.  The int8-MFMA form gives `value`; the NTT form is
-timed on the same batch and reported beside it.  Each form's step is also
-captured once as a HIP graph and replayed `steps` times (`graph_replay`:
-mean and median per replay, and whether the replays reproduce the eager
-outputs).
+before timing starts.  The int8 form gives `value`; the NTT form is timed on
+the same batch and reported beside it.  Both run on the double-precision
+transform kernel at these parameters; `int8_gemm` times the int8-MFMA kernels
+on the same batch, under an explicit plan.  Each form's step is also captured
+once as a HIP graph and replayed `steps` times (`graph_replay`: mean and
+median per replay, and whether the replays reproduce the eager outputs).
 
 Beside the main line: the mixed level of 16,384 independent gates with
 opcodes uniform over NAND/AND/OR/XOR/MUX (19,727 bootstraps, MUX counting
 two) timed for both forms (`mixed_level_16384`), the level chain of a
 one-gate and a 64-gate level (`level_chain`: graph replay per level
 against the summed bootstrap and key-switch kernel time), and a one-gate
-level in latency mode (`narrow_level`).
+level on the transform kernel and the int8 kernels (`narrow_level`).
 
 Keys and ciphertexts are seeded uniform arrays: real ones are
 indistinguishable from uniform under the LWE assumption and every kernel's
@@ -43,6 +44,7 @@ if ROOT not in sys.path:
 METRIC = ("gate bootstraps/sec on 1 MI355X (N=1024), int8-MFMA vs NTT form, "
           "bit-exact")
 PEAK_INT8_TOPS = 5000.0      # dense int8 MFMA, MI355X
+PEAK_F64_TFLOPS = 78.6       # f64 vector, MI355X
 DIGESTS = os.path.join(ROOT, "tests", "golden")
 
 
@@ -126,6 +128,30 @@ def ntt_mulmods_per_bootstrap(p):
     logN = p.N.bit_length() - 1
     per_ntt = (p.N // 2) * logN
     return p.n * ((2 * p.l + 2) * per_ntt + 2 * p.l * 2 * p.N)
+
+
+def fft_serves(p):
+    """Whether the double-precision kernel serves the set: its bound on a
+    coefficient's error before rounding is at most 1/4 (csrc/fft_form.hip),
+    digits fit 16 bits and the workgroup the LDS."""
+    M, m, R = p.N // 2, (p.N // 2).bit_length() - 1, 2 * p.l
+    err = (2 * R * M ** 1.5 * 2.0 ** (p.bg_bit - 1) * 2.0 ** 15 *
+           (15 * m + 2 * 2 ** 0.5 * R) * 2.0 ** -53)
+    row = M + M // 8 if p.N == 1024 else M
+    lds = max(R, 4) * row * 16 + 8 * p.N
+    return err <= 0.25 and p.bg_bit <= 16 and lds <= 160 * 1024
+
+
+def fft_flops_per_bootstrap(p):
+    """f64 operations one bootstrap issues (2 per fused multiply-add): 2l
+    forward transforms of M = N/2 points (6 fused multiply-adds per
+    butterfly), the pointwise sums for two components and two key halves,
+    four inverse transforms (10 operations per butterfly) and their
+    rounding."""
+    M = p.N // 2
+    m = M.bit_length() - 1
+    return p.n * (2 * p.l * (M // 2) * m * 12 + 2 * p.l * 4 * M * 8 +
+                  4 * ((M // 2) * m * 10 + 2 * M))
 
 
 def bootstraps_of(gates_np):
@@ -427,7 +453,33 @@ def main():
                 full * bootstraps / (rr["bs_kernel_ms"] * 1e-3) / 1e12, 1)
         return r
 
-    if main_form == "int8":
+    def fft_roof(rr, bootstraps):
+        fl = fft_flops_per_bootstrap(p)
+        ach = fl * bootstraps / (rr["bs_kernel_ms"] * 1e-3) / 1e12
+        return {"bound": "alu", "achieved": round(ach, 2),
+                "peak": PEAK_F64_TFLOPS, "unit": "TFLOP/s f64",
+                "frac": round(ach / PEAK_F64_TFLOPS, 4),
+                "kernel": "k_bootstrap_fft",
+                "per_launch": f"{bootstraps} bootstraps x {fl:.4g} f64 "
+                              "operations"}
+
+    fft = fft_serves(p)
+    gemm = None
+    if fft and "int8" in res:
+        # the int8-MFMA kernels on the same batch: the built-in plan, set
+        # explicitly
+        ctx.int8_plan(plan)
+        gemm, gemm_out = time_level(ctx, "int8", gates, wires, args.steps,
+                                    args.warmup,
+                                    out_rows=slice(2 * G, 3 * G),
+                                    bootstraps=G)
+        ctx.int8_plan(None)
+        gemm["same"] = bool(np.array_equal(gemm_out, outs["int8"]))
+        log(f"[bench] int8 GEMM kernels: {gemm['ms_per_step']:.3f} ms/step")
+    if fft:
+        roof = fft_roof(r, G)
+        roof["traffic"] = None
+    elif main_form == "int8":
         roof = int8_roof(r, G)
         roof.update({
             "traffic": (stored_traffic(kernel=roof["kernel"]) if G == 1024
@@ -442,17 +494,19 @@ def main():
         gbs = roof["traffic"] / (r["bs_kernel_ms"] * 1e-3) / 1e9
         roof["traffic_gb_per_s"] = round(gbs, 1)
         roof["traffic_frac_of_hbm"] = round(gbs / 8000.0, 5)
-    if main_form == "int8":
+    gemm_roof = int8_roof(gemm, G) if gemm else \
+        (roof if main_form == "int8" else None)
+    if gemm_roof is not None:
         # what the GPU sustains for this MFMA with random vs zero operand
         # bits (power limit); the published peak assumes the top clock
         ceil_rand = cggi.measure_int8_mfma(40000, True)
         ceil_zero = cggi.measure_int8_mfma(40000, False)
         log(f"[bench] bare int8 MFMA loop: {ceil_rand:.0f} TOP/s random "
             f"operands, {ceil_zero:.0f} TOP/s zero operands")
-        roof["measured_ceiling"] = {
+        gemm_roof["measured_ceiling"] = {
             "random_operands": round(ceil_rand, 1),
             "zero_operands": round(ceil_zero, 1), "unit": "TOP/s",
-            "frac_of_random": round(roof["achieved"] / ceil_rand, 4),
+            "frac_of_random": round(gemm_roof["achieved"] / ceil_rand, 4),
             "how": "bare v_mfma_i32_32x32x32_i8 loop, one 8-wave workgroup "
                    "per CU (cggi_measure_int8_mfma)"}
 
@@ -461,7 +515,8 @@ def main():
         "unit": "bootstraps/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": round(r["ms_per_step"], 4),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "int8" if main_form == "int8" else "u64",
+        "dtype": "f64" if fft else ("int8" if main_form == "int8" else
+                                    "u64"),
         "data": "synthetic",
         "config": {"workload": f"one level of {G} independent NAND gates, "
                                "n=630 N=1024 Bg=2^7 l=3 KS base 2^2 t=8",
@@ -476,9 +531,15 @@ def main():
             "value": round(rn["bootstraps_per_s"], 1),
             "ms_per_step": round(rn["ms_per_step"], 4),
             "graph_replay": rn["graph"],
-            "roofline": ntt_roof(rn, G)}
+            "roofline": fft_roof(rn, G) if fft else ntt_roof(rn, G)}
         line["int8_over_ntt"] = round(r["bootstraps_per_s"] /
                                       rn["bootstraps_per_s"], 3)
+    if gemm:
+        line["int8_gemm"] = {
+            "value": round(gemm["bootstraps_per_s"], 1),
+            "ms_per_step": round(gemm["ms_per_step"], 4),
+            "graph_replay": gemm["graph"], "roofline": gemm_roof,
+            "outputs_equal_value": gemm["same"]}
     line["forms_bit_identical"] = bool(forms_agree)
     if oracle_rows:
         line["outputs_equal_oracle"] = {
@@ -519,8 +580,9 @@ def main():
                 "kernel_ms": {"bootstrap": round(mr["bs_kernel_ms"], 3),
                               "keyswitch": round(mr["ks_kernel_ms"], 3)},
                 "graph_replay": mr["graph"],
-                "roofline": (int8_roof(mr, MB) if f == "int8"
-                             else ntt_roof(mr, MB)),
+                "roofline": (fft_roof(mr, MB) if fft else
+                             int8_roof(mr, MB) if f == "int8" else
+                             ntt_roof(mr, MB)),
                 "outputs_equal_oracle": (None if bad is None else
                                          f"{MG - len(bad)}/{MG} rows")}
         if len(mouts) == 2:
@@ -533,14 +595,19 @@ def main():
     if "int8" in res:
         line["level_chain"] = level_chain(ctx, p, dev)
     if "int8" in res and ctx.latency_groups() > 0:
-        # a narrow level: one NAND gate's bootstrap in latency mode (eight
-        # workgroups on eight CUs) and on the one-workgroup kernel
+        # a narrow level: one NAND gate's bootstrap on the double-precision
+        # kernel where it serves, and on the int8 kernels in latency mode
+        # (eight workgroups on eight CUs) and with one workgroup
         one = wires[:1].clone()
         big = torch.empty((1, p.N + 1), dtype=torch.int32, device=dev)
         narrow = {}
-        for mode, on in (("latency_mode_ms", True), ("one_workgroup_ms",
-                                                      False)):
+        modes = [("latency_mode_ms", True), ("one_workgroup_ms", False)]
+        if fft:
+            modes.insert(0, ("transform_ms", True))
+        for mode, on in modes:
             ctx.latency_mode(on)
+            if mode != "transform_ms":
+                ctx.int8_plan(ctx.int8_plan_get())
             ctx.bootstrap("int8", one, big)
             torch.cuda.synchronize()
             ctx.profile(True)
@@ -549,13 +616,15 @@ def main():
             bms, bn, _, _ = ctx.profile_read()
             ctx.profile(False)
             narrow[mode] = round(bms / max(bn, 1), 3)
+            ctx.int8_plan(None)
         ctx.latency_mode(True)
         try:
             ctx.check()
             line["narrow_level"] = dict(
                 bootstraps=1, **narrow,
-                kernels=["k_bootstrap_int8_split<1024, 3, 1, 8>",
-                         "k_bootstrap_int8<1024, 3, 1, 1>"])
+                kernels=(["k_bootstrap_fft"] if fft else []) +
+                ["k_bootstrap_int8_split<1024, 3, 1, 8>",
+                 "k_bootstrap_int8<1024, 3, 1, 1>"])
         except cggi.CggiError as e:
             # a latency-mode wait timed out (e.g. CUs taken by another
             # process): the figures above are void, the main line stands

@@ -49,7 +49,13 @@ typedef struct {
 } cggi_params_t;
 
 /* Forms of the negacyclic products inside the blind rotation.  Both give
- * bit-identical results.
+ * bit-identical results.  Where a double-precision transform is proven to
+ * round to the exact integers (csrc/fft_form.hip; Bg up to 2^13 or so, every
+ * parameter set of params.py), both forms run on that kernel, which is
+ * faster at every batch width; a context then keeps the key's transforms
+ * (64 * n*2l*N bytes) instead of the NTT form's.  The kernels below serve the
+ * other parameter sets and, for INT8, an explicit kernel plan
+ * (cggi_ctx_int8_plan).
  *  NTT : exact NTT modulo Q = 2^64 - 2^32 + 1 with the paper's generator
  *        (Section 5.4), centred lift, low 32 bits.
  *  INT8: exact split-limb block-Toeplitz GEMM on int8 MFMA with int32
@@ -91,9 +97,10 @@ int cggi_params_check(const cggi_params_t *params);
 
 /* Create a context on the current HIP device.  Reads d_bsk
  * ([n][2l][2][N]) once to derive the key forms selected by `forms` (a
- * bitmask of cggi_form_t): the NTT form stores the bootstrapping key
- * transformed mod Q (8 * n*2l*2*N bytes), the INT8 form stores its int8
- * limb windows (n*R*2*4*(N+64) bytes, R = 2l digit rows for Bg <= 2^7,
+ * bitmask of cggi_form_t): the key's double-precision transforms where they
+ * serve (64 * n*2l*N bytes; see cggi_form_t), else for the NTT form the
+ * bootstrapping key transformed mod Q (8 * n*2l*2*N bytes); the INT8 form
+ * stores its int8 limb windows (n*R*2*4*(N+64) bytes, R = 2l digit rows for Bg <= 2^7,
  * 4l for Bg <= 2^13) and, for N <= 1024, the key-only correction of its
  * offset digit operands (4 * n*2*N bytes).  For key-switch bases up to 2^4
  * the context also stores d_ksk as int8 limb blocks for the GEMM key switch
@@ -263,7 +270,10 @@ int cggi_measure_mulmod(int32_t iters, double *tmulmods);
  * on the context does nothing until cggi_ctx_check, which waits for the
  * device, returns CGGI_E_TIMEOUT if the word was set (clearing it and the
  * exchange buffers), else CGGI_OK.  Latency-mode launches on one context
- * must not run concurrently (they share its exchange buffers). */
+ * must not run concurrently (they share its exchange buffers).  Where the
+ * double-precision kernel serves the INT8 form (see cggi_form_t) latency
+ * mode runs only under an explicit plan; batches within its range still do
+ * nothing while the error word is set. */
 int cggi_ctx_latency_mode(cggi_ctx *ctx, int32_t enable);
 int cggi_ctx_latency_groups(const cggi_ctx *ctx, int32_t *groups);
 int cggi_ctx_check(cggi_ctx *ctx);
@@ -295,13 +305,13 @@ int cggi_ctx_latency_abort(cggi_ctx *ctx);
  * bootstraps one launch of each kind may take, 0 if the kind is
  * unavailable; latency-mode limits keep every workgroup resident).  All
  * kinds give bit-identical results; the plan only changes speed.  count = 0
- * restores the built-in plan (latency mode with eight, four, then two
- * workgroups while the tiles fit, then 1, 2 or 4 tiles per workgroup by
- * batch width;
- * see cggi_ctx_latency_mode).  While latency mode is off its entries are
+ * restores the built-in choice: the double-precision kernel where it serves
+ * (see cggi_form_t), else the built-in plan (latency mode with eight, four,
+ * then two workgroups while the tiles fit, then 1, 2 or 4 tiles per
+ * workgroup by batch width; see cggi_ctx_latency_mode).  While latency mode is off its entries are
  * skipped and their batches go to the next entry.  cggi_ctx_int8_plan_get
- * writes the plan in force (at most max entries; count = entries).  Host
- * state only: affects calls made afterwards.  Errors: CGGI_E_PARAM for a NULL
+ * writes the explicit or the built-in plan (at most max entries; count =
+ * entries).  Host state only: affects calls made afterwards.  Errors: CGGI_E_PARAM for a NULL
  * ctx or an invalid plan (nothing changes), CGGI_E_UNSUPPORTED without the
  * INT8 form, CGGI_E_SHAPE when max is too small. */
 enum {

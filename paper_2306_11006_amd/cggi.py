@@ -260,7 +260,8 @@ class Context:
     def int8_plan(self, plan=None):
         """Set the INT8 kernel plan: a list of (kind, cap) with kind a name
         of KINDS (or its index) and strictly increasing caps, the last at
-        least 2^24; None or [] restores the built-in plan."""
+        least 2^24; None or [] restores the built-in choice (the
+        double-precision kernel where it serves, else the built-in plan)."""
         plan = list(plan or [])
         n = len(plan)
         kinds = (ctypes.c_int32 * max(n, 1))(
@@ -270,7 +271,8 @@ class Context:
         _check(lib().cggi_ctx_int8_plan(self._h, kinds, caps, n))
 
     def int8_plan_get(self):
-        """The INT8 kernel plan in force, as [(kind name, cap)]."""
+        """The explicit or built-in INT8 kernel plan, as [(kind name,
+        cap)]."""
         kinds = (ctypes.c_int32 * 8)()
         caps = (ctypes.c_int32 * 8)()
         n = ctypes.c_int32()

@@ -118,6 +118,8 @@ static void free_ctx(Ctx *c)
     (void)hipFree(c->bsk_ntt);
     (void)hipFree(c->tw_fwd);
     (void)hipFree(c->tw_inv);
+    (void)hipFree(c->bsk_fft);
+    (void)hipFree(c->fft_tw);
     (void)hipFree(c->bsk_i8);
     (void)hipFree(c->corr_i8);
     (void)hipFree(c->bsk_k8);
@@ -261,6 +263,28 @@ static int64_t scratch_max_gates(const Shape &sh)
     return g;
 }
 
+int form_bootstrap(const Ctx *c, cggi_form_t form, const uint32_t *in,
+                   const uint32_t *testv, uint32_t *out, int B,
+                   const int32_t *d_count, hipStream_t s)
+{
+    const bool i8 = form == CGGI_FORM_INT8;
+    if (!c->bsk_fft || (i8 && c->plan_n > 0))
+        return i8 ? int8_bootstrap(c, in, testv, out, B, d_count, s)
+                  : ntt_bootstrap(c, in, testv, out, B, d_count, s);
+    // INT8 batches that latency mode would take keep its stop rule: they do
+    // nothing while the context's error word is set
+    int cap = 0;
+    if (i8 && c->split_on && c->x_err) {
+        int32_t kind[8], hi[8];
+        const int no = int8_active_plan(c, kind, hi);
+        for (int k = 0; k < no; ++k)
+            if (kind[k] <= 1 || kind[k] == 5)
+                cap = hi[k];
+    }
+    return fft_bootstrap(c, in, testv, out, B, d_count,
+                         cap > 0 ? c->x_err : nullptr, cap, s);
+}
+
 static void prof_clear(Ctx *c)
 {
     c->ev_used = 0;
@@ -335,7 +359,12 @@ int cggi_ctx_create(const cggi_params_t *params, const uint32_t *d_bsk,
         free_ctx(c);
         return rc;
     }
-    if (forms & CGGI_FORM_NTT) {
+    if ((rc = fft_make_key(c, d_bsk, s))) {
+        free_ctx(c);
+        return rc;
+    }
+    // with the FFT kernel the NTT form's own kernel is never launched
+    if ((forms & CGGI_FORM_NTT) && !c->bsk_fft) {
         if ((rc = ntt_make_tables(c, s)) || (rc = ntt_transform_bsk(c, d_bsk, s))) {
             free_ctx(c);
             return rc;
@@ -409,9 +438,7 @@ int cggi_bootstrap_batch(cggi_ctx *ctx, cggi_form_t form,
         return rc;
     hipStream_t s = (hipStream_t)stream;
     ProfScope ps(ctx, 0, s);
-    return form == CGGI_FORM_INT8
-               ? int8_bootstrap(ctx, d_in, d_testv, d_out, B, nullptr, s)
-               : ntt_bootstrap(ctx, d_in, d_testv, d_out, B, nullptr, s);
+    return form_bootstrap(ctx, form, d_in, d_testv, d_out, B, nullptr, s);
 }
 
 int cggi_keyswitch_batch(cggi_ctx *ctx, const uint32_t *d_in,

@@ -1,0 +1,778 @@
+// fft_form.hip -- the blind rotation with its products by a double-precision
+// transform whose rounding is proven exact, on gfx950.
+//
+// A CMux step (ArctyrEX Fig. 1 loop body) adds sum_r D_r * a_{r,c'} to each
+// accumulator component c' in Z_{2^32}[X]/(X^N+1).  Here every product is
+// taken in C[X]/(X^M - i), M = N/2: the map a -> sum_{j<M} (a_j + i a_{j+M})
+// X^j is a ring isomorphism from R[X]/(X^N+1), and X^M - i splits into M
+// linear factors, so a transform of M complex points turns a product into M
+// complex multiplications.
+//
+// Exactness.  Each key coefficient is split into two signed 16-bit halves,
+// K = k0 + 2^16 k1 (mod 2^32), with a transform each; the two sums
+// sum_r D_r k_{h,r} are integers, recovered by rounding and recombined mod
+// 2^32 (k1's sum only matters mod 2^16).  The rounding is right when the
+// error of every coefficient is below 1/2.  With u = 2^-53, R = 2l digit
+// polynomials of |digit| <= d, |k| <= 2^15 and m = log2 M stages:
+//  * a forward butterfly (a + wb by two fused multiply-adds per part, 2a
+//    minus that; w rounded to 53 bits) has an error of at most 5u times the
+//    2-norm of its outputs, an inverse one (sum, difference times conj(w))
+//    4u, so a transform's relative 2-norm error is at most 5mu;
+//  * the 2R fused multiply-adds of a pointwise sum add at most 2 sqrt(2) R u
+//    sum_r |D_r| |K_r| per point;
+//  * ||D_r o K_r||_2 <= max|K_r| ||D_r||_2 <= (sqrt(2) M 2^15)(sqrt(2) M d)
+//    (the same product bounds the other order), and the inverse transform
+//    divides 2-norms by sqrt(M); a coefficient's error is at most the 2-norm
+//    of the error vector.
+// Together a coefficient is off by less than
+//   E = 2 R M^1.5 d 2^15 (15 m + 2 sqrt(2) R) u:
+// 0.005 at the default set (N = 1024, Bg = 2^7, l = 3), 0.08 at the large
+// one (N = 2048, Bg = 2^10, l = 2).  A context uses this kernel when E is at
+// most 1/4 (fft_error_bound), for any key and any input, so the results are
+// the integers of the other kernels, bit for bit.
+//
+// Work split.  One workgroup per bootstrap.  A step has four phases between
+// barriers: (0) every thread rotates, subtracts and takes the digits of its
+// coefficients; (1) a wave per digit polynomial runs a whole forward
+// transform, PPL = 8 points per lane (16 at N = 2048); (2) a thread per
+// point sums the 2l products for the four outputs (component, key half);
+// (3) a wave per output runs the inverse transform, rounds and adds into
+// the accumulator.  A wave's transform is three register passes with two
+// exchanges through its own row of LDS, which need no barrier; rows are
+// padded or swizzled so that every 16 lanes of a 16-byte access fall in
+// distinct banks (a conflict-free exchange of 8 KB takes 140 cycles, three
+// quarters of it the write; an unswizzled one 360).
+//
+// What bounds it: at N = 1024 a step is a chain of about 9,000 cycles (LDS
+// writes and f64 issue of the six and four transform waves, the key's 192
+// KB through one CU's vector cache at 64 bytes a cycle hidden behind them),
+// 2.4 ms for up to 256 bootstraps against 2.8 to 8.5 ms for the int8
+// kernels and 10.3 ms for the modular transform; wider batches run at the
+// chip's power limit (the clock falls from 2.4 to 2.0 GHz).
+#include "internal.hpp"
+
+#include <cmath>
+#include <type_traits>
+#include <vector>
+
+namespace cggi {
+
+namespace {
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+// Index bits of a transform of M = N/2 points, from the top: a (RB bits,
+// the registers of pass 1), b (RB bits, pass 2), c (LAST bits, the stages of
+// pass 3, whose registers are b's low BS bits and c).
+template <int N> struct FCfg {
+    static constexpr int M = N / 2;
+    static constexpr int LOGM = __builtin_ctz(M);
+    static constexpr int RB = N == 2048 ? 4 : 3;
+    static constexpr int PPL = 1 << RB;          // points per lane
+    static constexpr int LPF = M / PPL;          // lanes per transform
+    static constexpr int FPW = 64 / LPF;         // transforms per wave
+    static constexpr int LAST = LOGM - 2 * RB;
+    static constexpr int BS = RB - LAST;
+    static constexpr int NTW = 1 << (RB - 1);    // twiddles per lane and pass
+    // bootstrap workgroup: a wave per digit polynomial of the usual sets
+    static constexpr int WAVES = N == 1024 ? 8 : (N == 256 ? 2 : 4);
+    static constexpr int THREADS = 64 * WAVES;
+    static constexpr int TW2 = NTW, TW3 = NTW + PPL * NTW; // table offsets
+    static constexpr int TWN = TW3 + LPF * NTW;  // table entries (complex)
+    static constexpr bool PAD = LAST == 3;       // padded rows (see fslot)
+    static constexpr int ROW = PAD ? M + M / 8 : M; // slots of an LDS row
+};
+
+// Slot of index (a, b, c) in a transform's exchange row, such that every 16
+// lanes of a 16-byte access fall in distinct banks.  At N = 1024 one pad slot
+// per 8 does that and leaves each access one lane base plus an immediate;
+// the other sizes swizzle (N = 2048 has no LDS left for a pad).
+template <int N> __device__ __forceinline__ int fslot(int a, int b, int c)
+{
+    using C = FCfg<N>;
+    if constexpr (C::PAD)
+        return a * 72 + b * 9 + c;
+    constexpr int AM = (1 << (4 - C::LAST)) - 1;
+    return (a << (C::RB + C::LAST)) | ((b ^ (a & AM)) << C::LAST) |
+           (c ^ (b >> C::BS));
+}
+
+// Order memory operations of one wave's lanes on LDS (they complete in
+// order; this only keeps the compiler from moving them).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+__device__ __forceinline__ void fft_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// (a, b) -> (a + wb, a - wb), w times i when ROT.
+template <bool ROT>
+__device__ __forceinline__ void bf_fwd(d2 &a, d2 &b, d2 w)
+{
+    d2 p;
+    if (!ROT) {
+        p.x = fma(-w.y, b.y, fma(w.x, b.x, a.x));
+        p.y = fma(w.y, b.x, fma(w.x, b.y, a.y));
+    } else {
+        p.x = fma(-w.y, b.x, fma(-w.x, b.y, a.x));
+        p.y = fma(-w.y, b.y, fma(w.x, b.x, a.y));
+    }
+    b.x = fma(2.0, a.x, -p.x);
+    b.y = fma(2.0, a.y, -p.y);
+    a = p;
+}
+
+// (a, b) -> (a + b, (a - b) conj(w)), w times i when ROT.
+template <bool ROT>
+__device__ __forceinline__ void bf_inv(d2 &a, d2 &b, d2 w)
+{
+    const d2 d = {a.x - b.x, a.y - b.y};
+    a.x += b.x;
+    a.y += b.y;
+    const double re = fma(d.x, w.x, d.y * w.y);
+    const double im = fma(d.y, w.x, -(d.x * w.y));
+    if (!ROT) {
+        b.x = re;
+        b.y = im;
+    } else {
+        b.x = im;
+        b.y = -re;
+    }
+}
+
+// NS stages over the low NS bits of the register index (the bits above them
+// select independent blocks with their own twiddles).  The node of a block
+// after bits beta_0.. has the twiddle of its first 2^(t-1) siblings times
+// i^beta_(t-1), so stage t of a block reads tw[(1 << t) / 2 + ..] only.
+template <int PPL, int NS, bool INV>
+__device__ __forceinline__ void reg_stages(d2 (&v)[PPL], const d2 *tw)
+{
+    constexpr int BLK = 1 << NS, PER = BLK / 2;   // twiddles per block
+#pragma unroll
+    for (int blk = 0; blk < PPL / BLK; ++blk)
+#pragma unroll
+        for (int tt = 0; tt < NS; ++tt) {
+            const int t = INV ? NS - 1 - tt : tt;
+            const int half = BLK >> (t + 1);      // distance of a butterfly
+            const d2 *wt = tw + blk * PER + (t == 0 ? 0 : (1 << (t - 1)));
+#pragma unroll
+            for (int g = 0; g < (1 << t); ++g) {  // bits beta_0 .. beta_(t-1)
+                // beta_0 is g's top bit; siblings in order of beta_0 + 2
+                // beta_1 + .. over the first t - 1 bits
+                int rev = 0;
+                for (int q = 0; q + 1 < t; ++q)
+                    rev |= ((g >> (t - 1 - q)) & 1) << q;
+                const bool rot = t > 0 && (g & 1);
+#pragma unroll
+                for (int k = 0; k < half; ++k) {
+                    d2 &x = v[blk * BLK + g * 2 * half + k];
+                    d2 &y = v[blk * BLK + g * 2 * half + k + half];
+                    if (INV) {
+                        if (rot)
+                            bf_inv<true>(x, y, wt[rev]);
+                        else
+                            bf_inv<false>(x, y, wt[rev]);
+                    } else {
+                        if (rot)
+                            bf_fwd<true>(x, y, wt[rev]);
+                        else
+                            bf_fwd<false>(x, y, wt[rev]);
+                    }
+                }
+            }
+        }
+}
+
+// A lane's twiddles: pass 1 (the same for every lane), 2 and 3.
+template <int N> struct Tw {
+    d2 w1[FCfg<N>::NTW], w2[FCfg<N>::NTW], w3[FCfg<N>::NTW];
+    __device__ __forceinline__ void load(const double *__restrict__ t, int lf)
+    {
+        using C = FCfg<N>;
+        const d2 *t2 = reinterpret_cast<const d2 *>(t);
+#pragma unroll
+        for (int k = 0; k < C::NTW; ++k) {
+            w1[k] = t2[k];
+            w2[k] = t2[C::TW2 + (lf >> C::LAST) * C::NTW + k];
+            w3[k] = t2[C::TW3 + lf * C::NTW + k];
+        }
+        // arrived before any loop: a use inside one would otherwise wait for
+        // every load the loop has in flight
+#pragma unroll
+        for (int k = 0; k < C::NTW; ++k) {
+            asm volatile("" : "+v"(w2[k].x), "+v"(w2[k].y));
+            asm volatile("" : "+v"(w3[k].x), "+v"(w3[k].y));
+        }
+    }
+};
+
+// Forward transform of the lane's points v (register index a, lane (b, c)),
+// through the transform's own LDS row; on return the registers are pass 3's
+// (b's low bits, c) on lane (a, b's high bits).
+// mid(0) and mid(1) run after the writes of the two exchanges.
+template <int N, class F>
+__device__ __forceinline__ void fft_forward(d2 (&v)[FCfg<N>::PPL], d2 *row,
+                                            int lf, const Tw<N> &tw, F mid)
+{
+    using C = FCfg<N>;
+    constexpr int CM = (1 << C::LAST) - 1, LM = (1 << C::BS) - 1;
+    reg_stages<C::PPL, C::RB, false>(v, tw.w1);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < C::PPL; ++k)
+        row[fslot<N>(k, lf >> C::LAST, lf & CM)] = v[k];
+    mid(0);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < C::PPL; ++k)
+        v[k] = row[fslot<N>(lf >> C::LAST, k, lf & CM)];
+    reg_stages<C::PPL, C::RB, false>(v, tw.w2);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < C::PPL; ++k)
+        row[fslot<N>(lf >> C::LAST, k, lf & CM)] = v[k];
+    mid(1);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < C::PPL; ++k)
+        v[k] = row[fslot<N>(lf >> C::LAST,
+                            ((lf & CM) << C::BS) | ((k >> C::LAST) & LM),
+                            k & CM)];
+    reg_stages<C::PPL, C::LAST, false>(v, tw.w3);
+    wave_sync();
+}
+
+// The inverse (unscaled) of fft_forward.
+template <int N>
+__device__ __forceinline__ void fft_inverse(d2 (&v)[FCfg<N>::PPL], d2 *row,
+                                            int lf, const Tw<N> &tw)
+{
+    using C = FCfg<N>;
+    constexpr int CM = (1 << C::LAST) - 1, LM = (1 << C::BS) - 1;
+    reg_stages<C::PPL, C::LAST, true>(v, tw.w3);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < C::PPL; ++k)
+        row[fslot<N>(lf >> C::LAST,
+                     ((lf & CM) << C::BS) | ((k >> C::LAST) & LM), k & CM)] =
+            v[k];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < C::PPL; ++k)
+        v[k] = row[fslot<N>(lf >> C::LAST, k, lf & CM)];
+    reg_stages<C::PPL, C::RB, true>(v, tw.w2);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < C::PPL; ++k)
+        row[fslot<N>(lf >> C::LAST, k, lf & CM)] = v[k];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < C::PPL; ++k)
+        v[k] = row[fslot<N>(k, lf >> C::LAST, lf & CM)];
+    reg_stages<C::PPL, C::RB, true>(v, tw.w1);
+    wave_sync();
+}
+
+// bsk [n][2l][2][N] -> transforms [n][2l][4][M] of the key halves times 1/M
+// (a power of two: exact), output o = 2 c' + h; point order as a transform
+// leaves it: register k of lane f at k LPF + f.  One wave per workgroup,
+// FPW transforms each.
+template <int N>
+__global__ __launch_bounds__(64) void k_fft_key(
+    const uint32_t *__restrict__ bsk, const double *__restrict__ tab,
+    double *__restrict__ out, int npoly)
+{
+    using C = FCfg<N>;
+    __shared__ __align__(16) double rows[C::FPW * C::ROW * 2];
+    const int lane = threadIdx.x, lf = lane % C::LPF, f = lane / C::LPF;
+    Tw<N> tw;
+    tw.load(tab, lf);
+    // polynomial index (i * 2l + r) * 4 + o
+    const int p = min((int)blockIdx.x * C::FPW + f, npoly - 1);
+    const int h = p & 1;
+    const uint32_t *src = bsk + (size_t)(p >> 1) * N;
+    auto half = [&](uint32_t x) -> double {
+        const int lo = (int16_t)(x & 0xFFFFu);
+        return h ? (double)(int16_t)((x - (uint32_t)lo) >> 16) : (double)lo;
+    };
+    d2 v[C::PPL];
+#pragma unroll
+    for (int k = 0; k < C::PPL; ++k) {
+        const int j = k * C::LPF + lf;
+        v[k].x = half(src[j]);
+        v[k].y = half(src[j + C::M]);
+    }
+    d2 *row = reinterpret_cast<d2 *>(rows) + f * C::ROW;
+    fft_forward<N>(v, row, lf, tw, [](int) {});
+    d2 *dst = reinterpret_cast<d2 *>(out) + (size_t)p * C::M;
+#pragma unroll
+    for (int k = 0; k < C::PPL; ++k) {
+        const double s = 1.0 / C::M;
+        dst[k * C::LPF + lf] = d2{v[k].x * s, v[k].y * s};
+    }
+}
+
+__device__ __forceinline__ uint32_t fft_modswitch(uint32_t u, int log2_2n)
+{
+    return (u + (1u << (31 - log2_2n))) >> (32 - log2_2n);
+}
+
+// LDS: rows [max(2l, 4)][ROW] complex, accumulator [2][N].
+size_t fft_smem(int N, int l)
+{
+    const int rows = 2 * l > 4 ? 2 * l : 4;
+    const int row = N == 1024 ? FCfg<1024>::ROW : N / 2;
+    return (size_t)rows * row * 16 + (size_t)2 * N * 4;
+}
+
+// L (gadget levels) is a compile-time constant for the sets in use, 0 reads
+// it at run time.  A thread reads its points' key values KR digit rows at a
+// time, a batch ahead of their use (the first batch before the barrier);
+// KR = 2L holds one point's whole column, read a step ahead.  WPE: waves per
+// SIMD the registers are budgeted for.
+template <int N, int L, int KR, int WPE>
+__global__ __launch_bounds__(FCfg<N>::THREADS)
+__attribute__((amdgpu_waves_per_eu(WPE)))
+void k_bootstrap_fft(
+    const double *__restrict__ key, const double *__restrict__ tab,
+    const uint32_t *__restrict__ in, const uint32_t *__restrict__ testv,
+    uint32_t *__restrict__ out, int B, const int32_t *__restrict__ d_count,
+    const uint32_t *__restrict__ stop, int stop_cap, int n, int beta, int l_rt)
+{
+    using C = FCfg<N>;
+    constexpr int M = C::M, PPL = C::PPL, LPF = C::LPF, FPW = C::FPW;
+    constexpr int ROW = C::ROW;
+    constexpr int T = C::THREADS;
+    constexpr int LOG2_2N = __builtin_ctz(2 * N);
+    const int l = L ? L : l_rt;
+    const int R = 2 * l;
+    extern __shared__ __align__(16) unsigned char smem[];
+    d2 *rows = reinterpret_cast<d2 *>(smem);
+    uint32_t *acc = reinterpret_cast<uint32_t *>(rows + (R > 4 ? R : 4) * ROW);
+
+    const int count = d_count ? min(B, *d_count) : B;
+    const int g = blockIdx.x;
+    if (g >= count)
+        return;
+    // narrow INT8 batches are refused while the latency-mode error word is
+    // set (cggi_ctx_latency_abort)
+    if (stop && count <= stop_cap && *stop)
+        return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lf = lane % LPF, f = lane / LPF;
+    const uint32_t *ct = in + (size_t)g * (n + 1);
+
+    // ACC = (0, X^(2N - b~) * v)
+    {
+        const int e = (2 * N - (int)fft_modswitch(ct[n], LOG2_2N)) & (2 * N - 1);
+        for (int m = tid; m < N; m += T) {
+            uint32_t v = testv ? testv[m] : (1u << 29);
+            int t = m + e;
+            if (t >= 2 * N) {
+                t -= 2 * N;
+            } else if (t >= N) {
+                t -= N;
+                v = 0u - v;
+            }
+            acc[t] = 0u;
+            acc[N + t] = v;
+        }
+    }
+    Tw<N> tw;
+    tw.load(tab, lf);
+
+    const uint32_t round_off = (beta * l < 32) ? (1u << (31 - beta * l)) : 0u;
+    // the digits' rounding offset, and their top bits: with those flipped a
+    // signed bit-field extract gives the digit in [-Bg/2, Bg/2)
+    uint32_t dig_off = round_off, dig_flip = 0;
+    for (int p = 1; p <= l; ++p) {
+        dig_off += (1u << (beta - 1)) << (32 - p * beta);
+        dig_flip |= (1u << (beta - 1)) << (32 - p * beta);
+    }
+    // key values in flight: batch bt covers rows KR (bt % NRB) .. of the
+    // thread's point bt / NRB
+    constexpr bool AHEAD = L > 0 && KR == 2 * L && M == T;
+    constexpr int NRB = L ? 2 * L / (KR ? KR : 1) : 1, NBT = NRB * (M / T);
+    constexpr int KB = L ? (AHEAD ? 1 : 2) : 1, KL = L ? KR * 4 : 1;
+    d2 kb[KB][KL];
+    const d2 *kpt = reinterpret_cast<const d2 *>(key) + tid;
+    auto key_issue = [&](int i, int bt, d2 (&dst)[KL], int q0, int q1) {
+        const d2 *src = kpt + ((size_t)i * R + (bt % NRB) * KR) * 4 * M +
+                        (bt / NRB) * T;
+#pragma unroll
+        for (int q = q0; q < q1; ++q)
+            dst[q] = src[q * M];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // forward transforms run on the last waves, inverse ones on the first
+    const int fw = wave - (C::WAVES * FPW > R ? C::WAVES - (R + FPW - 1) / FPW
+                                              : 0);
+
+    // The step loop, over the steps with a nonzero rotation (X^0 ACC - ACC
+    // = 0 decomposes to all-zero digits).  AHEAD has one copy per role so
+    // that each reads its keys at one place: waves without a forward
+    // transform in phase (1), those without an inverse one (role 3) a step
+    // ahead in phase (3), those with both (role 2) between forward passes.
+    auto steps = [&](auto role_c) {
+    constexpr int ROLE = decltype(role_c)::value;   // 0: any wave
+    uint32_t ev = 0;                // rotations of 64 steps, one per lane
+    unsigned long long live = 0;    // those still to come, nonzero ones
+    int i0 = -64;                   // first step of the 64
+    auto next = [&]() -> int {
+        while (!live) {
+            i0 += 64;
+            if (i0 >= n)
+                return n;
+            ev = fft_modswitch(ct[min(i0 + lane, n)], LOG2_2N) & (2 * N - 1);
+            live = __ballot(ev != 0 && i0 + lane < n);
+        }
+        const int b = __builtin_ctzll(live);
+        live &= live - 1;
+        return i0 + b;
+    };
+    int i = next();
+    if constexpr (ROLE == 3)
+        if (i < n)
+            key_issue(i, 0, kb[0], 0, KL);
+    while (i < n) {
+        const int e = __builtin_amdgcn_readlane(ev, i & 63);
+        const int i_nxt = next();
+        fft_barrier();   // ACC of the previous step complete
+        // (0) digits of X^e ACC - ACC: those of coefficients j and j + M of
+        // polynomial r side by side in dword j of row r, whose transform's
+        // wave alone reads them
+        {
+            constexpr int ITEMS = 2 * M / T;
+            uint32_t x[ITEMS][2], y[ITEMS][2];
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) {
+                const int idx = tid + it * T, c = idx / M, j = idx % M;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    x[it][q] = acc[c * N + ((j + q * M - e) & (N - 1))];
+                    y[it][q] = acc[c * N + j + q * M];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) {
+                const int idx = tid + it * T, c = idx / M, j = idx % M;
+                uint32_t w[2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    // all ones where the rotated index wrapped (bit N)
+                    const uint32_t mk = (uint32_t)__builtin_amdgcn_sbfe(
+                        j + q * M - e, LOG2_2N - 1, 1);
+                    w[q] = ((x[it][q] ^ mk) + (dig_off - y[it][q] - mk)) ^
+                           dig_flip;
+                }
+                uint32_t *dr = reinterpret_cast<uint32_t *>(
+                                   rows + c * l * ROW) + j;
+#pragma unroll
+                for (int p = 0; p < (L ? L : l); ++p) {
+                    const int sh = 32 - (p + 1) * beta;
+                    const uint32_t d0 = __builtin_amdgcn_sbfe(w[0], sh, beta);
+                    const uint32_t d1 = __builtin_amdgcn_sbfe(w[1], sh, beta);
+                    dr[p * ROW * 4] = __builtin_amdgcn_perm(d1, d0, 0x05040100);
+                }
+            }
+        }
+        fft_barrier();
+        // (1) their transforms
+        if constexpr (ROLE == 1)
+            key_issue(i, 0, kb[0], 0, KL);
+        for (int t0 = fw * FPW; ROLE != 1 && t0 >= 0 && t0 < R;
+             t0 += C::WAVES * FPW) {
+            // surplus lanes repeat the last polynomial's work (the same
+            // stores of the same values)
+            const int pol = FPW == 1 ? t0 : min(t0 + f, R - 1);
+            d2 *row = rows + pol * ROW;
+            const uint32_t *dr = reinterpret_cast<const uint32_t *>(row) + lf;
+            uint32_t dg[PPL];
+#pragma unroll
+            for (int k = 0; k < PPL; ++k)
+                dg[k] = dr[k * LPF];
+            d2 v[PPL];
+#pragma unroll
+            for (int k = 0; k < PPL; ++k) {
+                v[k].x = (double)(int16_t)dg[k];
+                v[k].y = (double)((int32_t)dg[k] >> 16);
+            }
+            fft_forward<N>(v, row, lf, tw, [&](int m) {
+                if constexpr (ROLE == 2)
+                    key_issue(i, 0, kb[0], m * KL / 2, (m + 1) * KL / 2);
+            });
+            if (ROLE)           // one transform per wave
+                t0 = R;
+#pragma unroll
+            for (int k = 0; k < PPL; ++k)
+                row[k * LPF + lf] = v[k];
+        }
+        if constexpr (L && !AHEAD)
+            key_issue(i, 0, kb[0], 0, KL);
+        fft_barrier();
+        // (2) the four outputs' sums over the digit polynomials, in place
+        // (a thread reads its point of every row before it writes it)
+        auto mac = [](d2 &s, d2 x, d2 k) {
+            s.x = fma(x.x, k.x, fma(-x.y, k.y, s.x));
+            s.y = fma(x.x, k.y, fma(x.y, k.x, s.y));
+        };
+        if constexpr (L > 0) {
+            d2 s[4];
+#pragma unroll
+            for (int bt = 0; bt < NBT; ++bt) {
+                const int j = tid + (bt / NRB) * T;
+                if (bt + 1 < NBT)
+                    key_issue(i, bt + 1, kb[(bt + 1) % KB], 0, KL);
+#pragma unroll
+                for (int rr = 0; rr < KR; ++rr) {
+                    const int r = (bt % NRB) * KR + rr;
+                    const d2 x = rows[r * ROW + j];
+#pragma unroll
+                    for (int o = 0; o < 4; ++o) {
+                        if (r == 0)
+                            s[o] = d2{0.0, 0.0};
+                        mac(s[o], x, kb[bt % KB][rr * 4 + o]);
+                    }
+                }
+                if (bt % NRB == NRB - 1)
+#pragma unroll
+                    for (int o = 0; o < 4; ++o)
+                        rows[o * ROW + j] = s[o];
+            }
+        } else {
+            const d2 *kp = reinterpret_cast<const d2 *>(key) +
+                           (size_t)i * R * 4 * M;
+            for (int j = tid; j < M; j += T) {
+                d2 s[4] = {};
+                for (int r = 0; r < R; ++r) {
+                    const d2 x = rows[r * ROW + j];
+#pragma unroll
+                    for (int o = 0; o < 4; ++o)
+                        mac(s[o], x, kp[(r * 4 + o) * M + j]);
+                }
+#pragma unroll
+                for (int o = 0; o < 4; ++o)
+                    rows[o * ROW + j] = s[o];
+            }
+        }
+        fft_barrier();
+        // (3) inverse transforms; the sums are integers below 2^51, so
+        // adding 1.5 * 2^52 leaves them rounded in the low mantissa bits
+        if constexpr (ROLE == 3)
+            key_issue(min(i_nxt, n - 1), 0, kb[0], 0, KL);
+        for (int t0 = wave * FPW; ROLE != 3 && t0 < 4;
+             t0 += C::WAVES * FPW) {
+            const int o = FPW == 1 ? t0 : t0 + f;
+            if (FPW > 1 && o >= 4)
+                break;
+            d2 *row = rows + o * ROW;
+            d2 v[PPL];
+#pragma unroll
+            for (int k = 0; k < PPL; ++k)
+                v[k] = row[k * LPF + lf];
+            fft_inverse<N>(v, row, lf, tw);
+            uint32_t *ao = acc + (o >> 1) * N + lf;
+            const int hs = 16 * (o & 1);
+#pragma unroll
+            for (int k = 0; k < PPL; ++k) {
+                const double magic = 6755399441055744.0;
+                const uint32_t re =
+                    (uint32_t)__double_as_longlong(v[k].x + magic) << hs;
+                const uint32_t im =
+                    (uint32_t)__double_as_longlong(v[k].y + magic) << hs;
+                __hip_atomic_fetch_add(ao + k * LPF, re, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(ao + k * LPF + M, im, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            if (ROLE)
+                t0 = 4;
+        }
+        i = i_nxt;
+    }
+    };
+    if constexpr (AHEAD) {
+        if (fw < 0)
+            steps(std::integral_constant<int, 1>{});
+        else if (wave < 4)
+            steps(std::integral_constant<int, 2>{});
+        else
+            steps(std::integral_constant<int, 3>{});
+    } else {
+        steps(std::integral_constant<int, 0>{});
+    }
+    __syncthreads();
+
+    // sample extraction of coefficient 0
+    uint32_t *o = out + (size_t)g * (N + 1);
+    for (int j = tid; j <= N; j += T) {
+        uint32_t v;
+        if (j == 0)
+            v = acc[0];
+        else if (j < N)
+            v = 0u - acc[N - j];
+        else
+            v = acc[N];
+        o[j] = v;
+    }
+}
+
+// Twiddle table: for a pass that starts at stage s in the node of prefix rho
+// (the earlier bits, first bit lowest), stage t's distinct twiddles
+// exp(i pi (phi / 2^t + sum_q beta_q 2^(q - t))), phi = (1/4 + rho) / 2^s,
+// over the bits beta_0 .. beta_(t-2) (the next bit multiplies by i).
+void push_twiddles(std::vector<double> &t, unsigned rho, int s, int ns)
+{
+    const long double pi = acosl(-1.0L);
+    const long double phi = (0.25L + rho) / (long double)(1u << s);
+    for (int st = 0; st < ns; ++st) {
+        const int cnt = st < 2 ? 1 : 1 << (st - 1);
+        for (int b = 0; b < cnt; ++b) {
+            const long double x =
+                pi * (phi + (long double)b) / (long double)(1 << st);
+            t.push_back((double)cosl(x));
+            t.push_back((double)sinl(x));
+        }
+    }
+}
+
+unsigned rev_bits(unsigned x, int bits)
+{
+    unsigned r = 0;
+    for (int i = 0; i < bits; ++i)
+        r |= ((x >> i) & 1u) << (bits - 1 - i);
+    return r;
+}
+
+template <int N> std::vector<double> fft_table()
+{
+    using C = FCfg<N>;
+    std::vector<double> t;
+    push_twiddles(t, 0, 0, C::RB);
+    for (int a = 0; a < C::PPL; ++a)
+        push_twiddles(t, rev_bits(a, C::RB), C::RB, C::RB);
+    for (int f = 0; f < C::LPF; ++f)
+        for (int bl = 0; bl < (1 << C::BS); ++bl) {
+            // prefix (a, b), b = (lane's low bits, bl)
+            const unsigned pre = ((unsigned)f << C::BS) | (unsigned)bl;
+            push_twiddles(t, rev_bits(pre, 2 * C::RB), 2 * C::RB, C::LAST);
+        }
+    return t;
+}
+
+// Rows of a key batch (L > 0): one point's whole column, a step ahead, at
+// N = 1024; two rows elsewhere.  Two waves per SIMD: 256 registers.
+template <int N> constexpr int FKR(int L) { return N == 1024 ? 2 * L : 2; }
+constexpr int FWPE = 2;
+
+template <int N, int L, int KR> int fft_attr1()
+{
+    CGGI_HIP_TRY(hipFuncSetAttribute(
+        reinterpret_cast<const void *>(&k_bootstrap_fft<N, L, KR, FWPE>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+    return CGGI_OK;
+}
+
+template <int N> int fft_attr(int l)
+{
+    return l == 3   ? fft_attr1<N, 3, FKR<N>(3)>()
+           : l == 2 ? fft_attr1<N, 2, FKR<N>(2)>()
+                    : fft_attr1<N, 0, 0>();
+}
+
+template <int N> int fft_key_t(Ctx *c, const uint32_t *bsk, hipStream_t s)
+{
+    using C = FCfg<N>;
+    const Shape &sh = c->sh;
+    const std::vector<double> t = fft_table<N>();
+    const int npoly = sh.n * 2 * sh.l * 4;
+    if (hipMalloc(&c->fft_tw, t.size() * sizeof(double)) != hipSuccess ||
+        hipMalloc(&c->bsk_fft, (size_t)npoly * C::M * 16) != hipSuccess) {
+        // the context then serves its forms with their own kernels
+        (void)hipGetLastError();
+        (void)hipFree(c->fft_tw);
+        c->fft_tw = c->bsk_fft = nullptr;
+        return CGGI_OK;
+    }
+    CGGI_HIP_TRY(hipMemcpyAsync(c->fft_tw, t.data(), t.size() * sizeof(double),
+                                hipMemcpyHostToDevice, s));
+    CGGI_HIP_TRY(hipStreamSynchronize(s));   // t leaves scope
+    hipLaunchKernelGGL(k_fft_key<N>, dim3((npoly + C::FPW - 1) / C::FPW),
+                       dim3(64), 0, s, bsk, c->fft_tw, c->bsk_fft, npoly);
+    CGGI_HIP_TRY(hipGetLastError());
+    return fft_attr<N>(sh.l);
+}
+
+template <int N>
+int fft_launch(const Ctx *c, const uint32_t *in, const uint32_t *testv,
+               uint32_t *out, int B, const int32_t *d_count,
+               const uint32_t *stop, int stop_cap, hipStream_t s)
+{
+    const Shape &sh = c->sh;
+    const size_t smem = fft_smem(N, sh.l);
+#define FFT_LAUNCH(LL, KR, WPE)                                              \
+    hipLaunchKernelGGL((k_bootstrap_fft<N, LL, KR, WPE>), dim3(B),           \
+                       dim3(FCfg<N>::THREADS), smem, s, c->bsk_fft,          \
+                       c->fft_tw, in, testv, out, B, d_count, stop,          \
+                       stop_cap, sh.n, sh.beta, sh.l)
+    if (sh.l == 3)
+        FFT_LAUNCH(3, FKR<N>(3), FWPE);
+    else if (sh.l == 2)
+        FFT_LAUNCH(2, FKR<N>(2), FWPE);
+    else
+        FFT_LAUNCH(0, 0, FWPE);
+#undef FFT_LAUNCH
+    CGGI_HIP_TRY(hipGetLastError());
+    return CGGI_OK;
+}
+
+} // namespace
+
+double fft_error_bound(const Shape &sh)
+{
+    const double M = sh.N / 2, m = sh.log2N - 1, R = 2.0 * sh.l;
+    return 2.0 * R * M * std::sqrt(M) * std::ldexp(1.0, sh.beta - 1) *
+           32768.0 * (15.0 * m + 2.0 * std::sqrt(2.0) * R) *
+           std::ldexp(1.0, -53);
+}
+
+int fft_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s)
+{
+    if (fft_error_bound(c->sh) > 0.25 || c->sh.beta > 16 ||
+        fft_smem(c->sh.N, c->sh.l) > 160 * 1024)
+        return CGGI_OK;                  // not available at these parameters
+    switch (c->sh.N) {
+    case 256: return fft_key_t<256>(c, bsk, s);
+    case 512: return fft_key_t<512>(c, bsk, s);
+    case 1024: return fft_key_t<1024>(c, bsk, s);
+    default: return fft_key_t<2048>(c, bsk, s);
+    }
+}
+
+int fft_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
+                  uint32_t *out, int B, const int32_t *d_count,
+                  const uint32_t *stop, int stop_cap, hipStream_t s)
+{
+    switch (c->sh.N) {
+    case 256:
+        return fft_launch<256>(c, in, testv, out, B, d_count, stop, stop_cap, s);
+    case 512:
+        return fft_launch<512>(c, in, testv, out, B, d_count, stop, stop_cap, s);
+    case 1024:
+        return fft_launch<1024>(c, in, testv, out, B, d_count, stop, stop_cap, s);
+    default:
+        return fft_launch<2048>(c, in, testv, out, B, d_count, stop, stop_cap, s);
+    }
+}
+
+} // namespace cggi

@@ -36,6 +36,10 @@ struct cggi_ctx {
     uint64_t *bsk_ntt = nullptr;  // [n][2l][2][N] mod Q, bit-reversed order
     uint64_t *tw_fwd = nullptr;   // [N] psi^bitrev(i)
     uint64_t *tw_inv = nullptr;   // [N] psi^-bitrev(i)
+    // FFT kernel (fft_form.hip), serving both forms; null where its error
+    // bound does not prove the rounding
+    double *bsk_fft = nullptr;    // [n][2l][4][N/2] complex, key halves
+    double *fft_tw = nullptr;     // its twiddle table
     // INT8 form
     int8_t *bsk_i8 = nullptr;     // [n][R][2][4][elen] limb windows
     uint32_t *corr_i8 = nullptr;  // [n][2][N] digit-offset correction (N <= 1024)
@@ -104,6 +108,17 @@ int ntt_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
                   uint32_t *out, int B, const int32_t *d_count,
                   hipStream_t s);
 
+// FFT kernel: bound on the error of a coefficient before rounding, key
+// transforms at context creation (a no-op where the bound exceeds 1/4 or
+// the workgroup the LDS), and a launch of B bootstraps (at most *d_count
+// when given).  With `stop`, a launch of at most stop_cap bootstraps does
+// nothing while *stop is set.
+double fft_error_bound(const Shape &sh);
+int fft_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s);
+int fft_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
+                  uint32_t *out, int B, const int32_t *d_count,
+                  const uint32_t *stop, int stop_cap, hipStream_t s);
+
 int int8_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s);
 int int8_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
                    uint32_t *out, int B, const int32_t *d_count,
@@ -122,6 +137,12 @@ int int8_split_reset(Ctx *c);
 // latency-mode entries dropped while latency mode is off.  Returns the
 // number of entries (at most 8).
 int int8_active_plan(const Ctx *c, int32_t *kind, int32_t *cap);
+
+// Bootstrap B ciphertexts in the given form: the FFT kernel where the
+// context has it and no INT8 plan was set, else the form's own kernels.
+int form_bootstrap(const Ctx *c, cggi_form_t form, const uint32_t *in,
+                   const uint32_t *testv, uint32_t *out, int B,
+                   const int32_t *d_count, hipStream_t s);
 
 // Key switch.  in_a/in_b: optional second input added before switching
 // (MUX combine); the plain batch call passes null maps.

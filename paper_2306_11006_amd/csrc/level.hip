@@ -167,11 +167,8 @@ int level_launch(Ctx *c, cggi_form_t form, const cggi_gate_t *gates, int G,
     int rc;
     {
         ProfScope ps(pc, 0, s);
-        rc = form == CGGI_FORM_INT8
-                 ? int8_bootstrap(c, ws.small, nullptr, ws.big, 2 * G,
-                                  ws.count, s)
-                 : ntt_bootstrap(c, ws.small, nullptr, ws.big, 2 * G,
-                                 ws.count, s);
+        rc = form_bootstrap(c, form, ws.small, nullptr, ws.big, 2 * G,
+                            ws.count, s);
     }
     if (rc != CGGI_OK)
         return rc;
