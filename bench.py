@@ -137,7 +137,7 @@ def fft_serves(p):
     M, m, R = p.N // 2, (p.N // 2).bit_length() - 1, 2 * p.l
     err = (2 * R * M ** 1.5 * 2.0 ** (p.bg_bit - 1) * 2.0 ** 15 *
            (15 * m + 2 * 2 ** 0.5 * R) * 2.0 ** -53)
-    row = M + M // 8 if p.N == 1024 else M
+    row = M + M // 8 if p.N >= 1024 else M
     lds = max(R, 4) * row * 16 + 8 * p.N
     return err <= 0.25 and p.bg_bit <= 16 and lds <= 160 * 1024
 

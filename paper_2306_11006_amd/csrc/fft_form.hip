@@ -61,32 +61,37 @@ namespace {
 
 typedef double d2 __attribute__((ext_vector_type(2)));
 
-// Index bits of a transform of M = N/2 points, from the top: a (RB bits,
+// A transform of M = N/2 points is H transforms of MS points, one per wave:
+// at N = 2048 (H = 2) those of the even and the odd coefficients, E and O,
+// both at the roots Y of Y^MS = i, which the pointwise phase combines into
+// the points E(X^2) +- X O(X^2) as it reads them (and splits its sums the
+// same way).  Index bits of an MS-point transform, from the top: a (RB bits,
 // the registers of pass 1), b (RB bits, pass 2), c (LAST bits, the stages of
 // pass 3, whose registers are b's low BS bits and c).
 template <int N> struct FCfg {
     static constexpr int M = N / 2;
-    static constexpr int LOGM = __builtin_ctz(M);
-    static constexpr int RB = N == 2048 ? 4 : 3;
+    static constexpr int H = N == 2048 ? 2 : 1;
+    static constexpr int MS = M / H;
+    static constexpr int LOGM = __builtin_ctz(MS);
+    static constexpr int RB = 3;
     static constexpr int PPL = 1 << RB;          // points per lane
-    static constexpr int LPF = M / PPL;          // lanes per transform
+    static constexpr int LPF = MS / PPL;         // lanes per transform
     static constexpr int FPW = 64 / LPF;         // transforms per wave
     static constexpr int LAST = LOGM - 2 * RB;
     static constexpr int BS = RB - LAST;
     static constexpr int NTW = 1 << (RB - 1);    // twiddles per lane and pass
-    // bootstrap workgroup: a wave per digit polynomial of the usual sets
-    static constexpr int WAVES = N == 1024 ? 8 : (N == 256 ? 2 : 4);
-    static constexpr int THREADS = 64 * WAVES;
+    // bootstrap workgroup: a thread per point of an MS-point transform
+    static constexpr int THREADS = MS, WAVES = MS / 64;
     static constexpr int TW2 = NTW, TW3 = NTW + PPL * NTW; // table offsets
-    static constexpr int TWN = TW3 + LPF * NTW;  // table entries (complex)
+    static constexpr int TWX = TW3 + LPF * NTW;  // H = 2: [MS] values X
     static constexpr bool PAD = LAST == 3;       // padded rows (see fslot)
-    static constexpr int ROW = PAD ? M + M / 8 : M; // slots of an LDS row
+    static constexpr int ROW = PAD ? MS + MS / 8 : MS; // slots of an LDS row
 };
 
 // Slot of index (a, b, c) in a transform's exchange row, such that every 16
-// lanes of a 16-byte access fall in distinct banks.  At N = 1024 one pad slot
-// per 8 does that and leaves each access one lane base plus an immediate;
-// the other sizes swizzle (N = 2048 has no LDS left for a pad).
+// lanes of a 16-byte access fall in distinct banks.  For 512 points one pad
+// slot per 8 does that and leaves each access one lane base plus an
+// immediate; the shorter transforms swizzle.
 template <int N> __device__ __forceinline__ int fslot(int a, int b, int c)
 {
     using C = FCfg<N>;
@@ -251,9 +256,9 @@ __device__ __forceinline__ void fft_forward(d2 (&v)[FCfg<N>::PPL], d2 *row,
 }
 
 // The inverse (unscaled) of fft_forward.
-template <int N>
+template <int N, class F>
 __device__ __forceinline__ void fft_inverse(d2 (&v)[FCfg<N>::PPL], d2 *row,
-                                            int lf, const Tw<N> &tw)
+                                            int lf, const Tw<N> &tw, F mid)
 {
     using C = FCfg<N>;
     constexpr int CM = (1 << C::LAST) - 1, LM = (1 << C::BS) - 1;
@@ -264,6 +269,7 @@ __device__ __forceinline__ void fft_inverse(d2 (&v)[FCfg<N>::PPL], d2 *row,
         row[fslot<N>(lf >> C::LAST,
                      ((lf & CM) << C::BS) | ((k >> C::LAST) & LM), k & CM)] =
             v[k];
+    mid(0);
     wave_sync();
 #pragma unroll
     for (int k = 0; k < C::PPL; ++k)
@@ -273,6 +279,7 @@ __device__ __forceinline__ void fft_inverse(d2 (&v)[FCfg<N>::PPL], d2 *row,
 #pragma unroll
     for (int k = 0; k < C::PPL; ++k)
         row[fslot<N>(lf >> C::LAST, k, lf & CM)] = v[k];
+    mid(1);
     wave_sync();
 #pragma unroll
     for (int k = 0; k < C::PPL; ++k)
@@ -282,15 +289,17 @@ __device__ __forceinline__ void fft_inverse(d2 (&v)[FCfg<N>::PPL], d2 *row,
 }
 
 // bsk [n][2l][2][N] -> transforms [n][2l][4][M] of the key halves times 1/M
-// (a power of two: exact), output o = 2 c' + h; point order as a transform
-// leaves it: register k of lane f at k LPF + f.  One wave per workgroup,
-// FPW transforms each.
+// (a power of two: exact), output o = 2 c' + h; points [H][MS] as a
+// transform leaves them: register k of lane f at k LPF + f; for H = 2 first
+// the MS values at X, then those at -X.  One wave per workgroup, FPW
+// polynomials each.
 template <int N>
 __global__ __launch_bounds__(64) void k_fft_key(
     const uint32_t *__restrict__ bsk, const double *__restrict__ tab,
     double *__restrict__ out, int npoly)
 {
     using C = FCfg<N>;
+    constexpr int H = C::H;
     __shared__ __align__(16) double rows[C::FPW * C::ROW * 2];
     const int lane = threadIdx.x, lf = lane % C::LPF, f = lane / C::LPF;
     Tw<N> tw;
@@ -303,20 +312,29 @@ __global__ __launch_bounds__(64) void k_fft_key(
         const int lo = (int16_t)(x & 0xFFFFu);
         return h ? (double)(int16_t)((x - (uint32_t)lo) >> 16) : (double)lo;
     };
-    d2 v[C::PPL];
-#pragma unroll
-    for (int k = 0; k < C::PPL; ++k) {
-        const int j = k * C::LPF + lf;
-        v[k].x = half(src[j]);
-        v[k].y = half(src[j + C::M]);
-    }
+    d2 v[H][C::PPL];
     d2 *row = reinterpret_cast<d2 *>(rows) + f * C::ROW;
-    fft_forward<N>(v, row, lf, tw, [](int) {});
+#pragma unroll
+    for (int q = 0; q < H; ++q) {
+#pragma unroll
+        for (int k = 0; k < C::PPL; ++k) {
+            const int j = H * (k * C::LPF + lf) + q;
+            v[q][k].x = half(src[j]);
+            v[q][k].y = half(src[j + C::M]);
+        }
+        fft_forward<N>(v[q], row, lf, tw, [](int) {});
+    }
     d2 *dst = reinterpret_cast<d2 *>(out) + (size_t)p * C::M;
 #pragma unroll
     for (int k = 0; k < C::PPL; ++k) {
         const double s = 1.0 / C::M;
-        dst[k * C::LPF + lf] = d2{v[k].x * s, v[k].y * s};
+        const int j = k * C::LPF + lf;
+        if constexpr (H == 2)
+            bf_fwd<false>(v[0][k], v[H - 1][k],
+                          reinterpret_cast<const d2 *>(tab)[C::TWX + j]);
+#pragma unroll
+        for (int q = 0; q < H; ++q)
+            dst[q * C::MS + j] = d2{v[q][k].x * s, v[q][k].y * s};
     }
 }
 
@@ -325,19 +343,27 @@ __device__ __forceinline__ uint32_t fft_modswitch(uint32_t u, int log2_2n)
     return (u + (1u << (31 - log2_2n))) >> (32 - log2_2n);
 }
 
-// LDS: rows [max(2l, 4)][ROW] complex, accumulator [2][N].
-size_t fft_smem(int N, int l)
+// LDS: rows [max(2l, 4)][H][ROW] complex, accumulator [2][N] (H = 2: the even
+// coefficients of a component, then its odd ones).
+template <int N> size_t fft_smem_n(int l)
 {
     const int rows = 2 * l > 4 ? 2 * l : 4;
-    const int row = N == 1024 ? FCfg<1024>::ROW : N / 2;
-    return (size_t)rows * row * 16 + (size_t)2 * N * 4;
+    return (size_t)rows * FCfg<N>::H * FCfg<N>::ROW * 16 + (size_t)2 * N * 4;
+}
+
+size_t fft_smem(int N, int l)
+{
+    return N == 256    ? fft_smem_n<256>(l)
+           : N == 512  ? fft_smem_n<512>(l)
+           : N == 1024 ? fft_smem_n<1024>(l)
+                       : fft_smem_n<2048>(l);
 }
 
 // L (gadget levels) is a compile-time constant for the sets in use, 0 reads
-// it at run time.  A thread reads its points' key values KR digit rows at a
-// time, a batch ahead of their use (the first batch before the barrier);
-// KR = 2L holds one point's whole column, read a step ahead.  WPE: waves per
-// SIMD the registers are budgeted for.
+// it at run time.  A thread reads the key values of its slot (H points) KR
+// digit rows at a time, a batch ahead of their use (the first batch before
+// the barrier); KR = 2L holds the whole column, read during the transforms.
+// WPE: waves per SIMD the registers are budgeted for.
 template <int N, int L, int KR, int WPE>
 __global__ __launch_bounds__(FCfg<N>::THREADS)
 __attribute__((amdgpu_waves_per_eu(WPE)))
@@ -349,14 +375,16 @@ void k_bootstrap_fft(
 {
     using C = FCfg<N>;
     constexpr int M = C::M, PPL = C::PPL, LPF = C::LPF, FPW = C::FPW;
-    constexpr int ROW = C::ROW;
+    constexpr int ROW = C::ROW, H = C::H, MS = C::MS;
     constexpr int T = C::THREADS;
     constexpr int LOG2_2N = __builtin_ctz(2 * N);
     const int l = L ? L : l_rt;
     const int R = 2 * l;
     extern __shared__ __align__(16) unsigned char smem[];
     d2 *rows = reinterpret_cast<d2 *>(smem);
-    uint32_t *acc = reinterpret_cast<uint32_t *>(rows + (R > 4 ? R : 4) * ROW);
+    uint32_t *acc = reinterpret_cast<uint32_t *>(rows + (R > 4 ? R : 4) * H * ROW);
+    // accumulator word of coefficient t of a component
+    auto aidx = [](int t) { return H == 2 ? (t & 1) * M + (t >> 1) : t; };
 
     const int count = d_count ? min(B, *d_count) : B;
     const int g = blockIdx.x;
@@ -383,8 +411,8 @@ void k_bootstrap_fft(
                 t -= N;
                 v = 0u - v;
             }
-            acc[t] = 0u;
-            acc[N + t] = v;
+            acc[aidx(t)] = 0u;
+            acc[N + aidx(t)] = v;
         }
     }
     Tw<N> tw;
@@ -398,30 +426,38 @@ void k_bootstrap_fft(
         dig_off += (1u << (beta - 1)) << (32 - p * beta);
         dig_flip |= (1u << (beta - 1)) << (32 - p * beta);
     }
-    // key values in flight: batch bt covers rows KR (bt % NRB) .. of the
-    // thread's point bt / NRB
-    constexpr bool AHEAD = L > 0 && KR == 2 * L && M == T;
-    constexpr int NRB = L ? 2 * L / (KR ? KR : 1) : 1, NBT = NRB * (M / T);
-    constexpr int KB = L ? (AHEAD ? 1 : 2) : 1, KL = L ? KR * 4 : 1;
+    // X of this thread's slot (H = 2)
+    d2 xs = {0.0, 0.0};
+    if constexpr (H == 2) {
+        xs = reinterpret_cast<const d2 *>(tab)[C::TWX + tid];
+        asm volatile("" : "+v"(xs.x), "+v"(xs.y));
+    }
+    // key values in flight: batch bt covers rows KR bt .. of the slot
+    constexpr bool AHEAD = L > 0 && KR == 2 * L;
+    constexpr int NBT = L ? 2 * L / (KR ? KR : 1) : 1;
+    constexpr int KB = L ? (AHEAD ? 1 : 2) : 1, KL = L ? KR * 4 * H : 1;
     d2 kb[KB][KL];
     const d2 *kpt = reinterpret_cast<const d2 *>(key) + tid;
     auto key_issue = [&](int i, int bt, d2 (&dst)[KL], int q0, int q1) {
-        const d2 *src = kpt + ((size_t)i * R + (bt % NRB) * KR) * 4 * M +
-                        (bt / NRB) * T;
+        const d2 *src = kpt + ((size_t)i * R + bt * KR) * 4 * M;
 #pragma unroll
         for (int q = q0; q < q1; ++q)
-            dst[q] = src[q * M];
+            dst[q] = src[q * MS];
         __builtin_amdgcn_sched_barrier(0);
     };
     // forward transforms run on the last waves, inverse ones on the first
-    const int fw = wave - (C::WAVES * FPW > R ? C::WAVES - (R + FPW - 1) / FPW
-                                              : 0);
+    const int nf = R * H, ni = 4 * H;
+    const int fw = wave - (C::WAVES * FPW > nf ? C::WAVES - (nf + FPW - 1) / FPW
+                                               : 0);
 
     // The step loop, over the steps with a nonzero rotation (X^0 ACC - ACC
     // = 0 decomposes to all-zero digits).  AHEAD has one copy per role so
-    // that each reads its keys at one place: waves without a forward
-    // transform in phase (1), those without an inverse one (role 3) a step
-    // ahead in phase (3), those with both (role 2) between forward passes.
+    // that each reads its keys at fixed places: waves without a forward
+    // transform (role 1) in phase (1), those without an inverse one (role 3)
+    // a step ahead in phase (3), those with both between forward passes
+    // (role 2; with eight waves of both, role 4, half of them between the
+    // previous step's inverse passes, or the vector cache's 64 bytes a cycle
+    // would hold up phase (1)).
     auto steps = [&](auto role_c) {
     constexpr int ROLE = decltype(role_c)::value;   // 0: any wave
     uint32_t ev = 0;                // rotations of 64 steps, one per lane
@@ -440,49 +476,52 @@ void k_bootstrap_fft(
         return i0 + b;
     };
     int i = next();
-    if constexpr (ROLE == 3)
+    if constexpr (ROLE >= 3)
         if (i < n)
-            key_issue(i, 0, kb[0], 0, KL);
+            key_issue(i, 0, kb[0], 0, ROLE == 3 ? KL : KL / 2);
     while (i < n) {
         const int e = __builtin_amdgcn_readlane(ev, i & 63);
         const int i_nxt = next();
         fft_barrier();   // ACC of the previous step complete
         // (0) digits of X^e ACC - ACC: those of coefficients j and j + M of
-        // polynomial r side by side in dword j of row r, whose transform's
-        // wave alone reads them
+        // polynomial r side by side in dword j / H of row (r, j mod H),
+        // whose transform's wave alone reads them
         {
-            constexpr int ITEMS = 2 * M / T;
+            constexpr int ITEMS = 2 * H;
             uint32_t x[ITEMS][2], y[ITEMS][2];
+            // item it: component it / H, coefficients j and j + M
+            auto coef = [&](int it) { return H * tid + it % H; };
 #pragma unroll
-            for (int it = 0; it < ITEMS; ++it) {
-                const int idx = tid + it * T, c = idx / M, j = idx % M;
+            for (int it = 0; it < ITEMS; ++it)
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
-                    x[it][q] = acc[c * N + ((j + q * M - e) & (N - 1))];
-                    y[it][q] = acc[c * N + j + q * M];
+                    const int t = coef(it) + q * M;
+                    const uint32_t *ac = acc + it / H * N;
+                    x[it][q] = ac[aidx((t - e) & (N - 1))];
+                    y[it][q] = ac[aidx(t)];
                 }
-            }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
-                const int idx = tid + it * T, c = idx / M, j = idx % M;
                 uint32_t w[2];
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
                     // all ones where the rotated index wrapped (bit N)
                     const uint32_t mk = (uint32_t)__builtin_amdgcn_sbfe(
-                        j + q * M - e, LOG2_2N - 1, 1);
+                        coef(it) + q * M - e, LOG2_2N - 1, 1);
                     w[q] = ((x[it][q] ^ mk) + (dig_off - y[it][q] - mk)) ^
                            dig_flip;
                 }
                 uint32_t *dr = reinterpret_cast<uint32_t *>(
-                                   rows + c * l * ROW) + j;
+                                   rows + (it / H * l * H + it % H) * ROW) +
+                               tid;
 #pragma unroll
                 for (int p = 0; p < (L ? L : l); ++p) {
                     const int sh = 32 - (p + 1) * beta;
                     const uint32_t d0 = __builtin_amdgcn_sbfe(w[0], sh, beta);
                     const uint32_t d1 = __builtin_amdgcn_sbfe(w[1], sh, beta);
-                    dr[p * ROW * 4] = __builtin_amdgcn_perm(d1, d0, 0x05040100);
+                    dr[p * H * ROW * 4] =
+                        __builtin_amdgcn_perm(d1, d0, 0x05040100);
                 }
             }
         }
@@ -490,11 +529,11 @@ void k_bootstrap_fft(
         // (1) their transforms
         if constexpr (ROLE == 1)
             key_issue(i, 0, kb[0], 0, KL);
-        for (int t0 = fw * FPW; ROLE != 1 && t0 >= 0 && t0 < R;
+        for (int t0 = fw * FPW; ROLE != 1 && t0 >= 0 && t0 < nf;
              t0 += C::WAVES * FPW) {
             // surplus lanes repeat the last polynomial's work (the same
             // stores of the same values)
-            const int pol = FPW == 1 ? t0 : min(t0 + f, R - 1);
+            const int pol = FPW == 1 ? t0 : min(t0 + f, nf - 1);
             d2 *row = rows + pol * ROW;
             const uint32_t *dr = reinterpret_cast<const uint32_t *>(row) + lf;
             uint32_t dg[PPL];
@@ -510,9 +549,11 @@ void k_bootstrap_fft(
             fft_forward<N>(v, row, lf, tw, [&](int m) {
                 if constexpr (ROLE == 2)
                     key_issue(i, 0, kb[0], m * KL / 2, (m + 1) * KL / 2);
+                if constexpr (ROLE == 4)
+                    key_issue(i, 0, kb[0], (m + 2) * KL / 4, (m + 3) * KL / 4);
             });
             if (ROLE)           // one transform per wave
-                t0 = R;
+                t0 = nf;
 #pragma unroll
             for (int k = 0; k < PPL; ++k)
                 row[k * LPF + lf] = v[k];
@@ -526,62 +567,74 @@ void k_bootstrap_fft(
             s.x = fma(x.x, k.x, fma(-x.y, k.y, s.x));
             s.y = fma(x.x, k.y, fma(x.y, k.x, s.y));
         };
+        // a row's points in the thread's slot
+        auto points = [&](int r, d2 (&x)[H]) {
+#pragma unroll
+            for (int q = 0; q < H; ++q)
+                x[q] = rows[(r * H + q) * ROW + tid];
+            if constexpr (H == 2)
+                bf_fwd<false>(x[0], x[H - 1], xs);
+        };
+        d2 s[4][H] = {};
         if constexpr (L > 0) {
-            d2 s[4];
 #pragma unroll
             for (int bt = 0; bt < NBT; ++bt) {
-                const int j = tid + (bt / NRB) * T;
                 if (bt + 1 < NBT)
                     key_issue(i, bt + 1, kb[(bt + 1) % KB], 0, KL);
 #pragma unroll
                 for (int rr = 0; rr < KR; ++rr) {
-                    const int r = (bt % NRB) * KR + rr;
-                    const d2 x = rows[r * ROW + j];
-#pragma unroll
-                    for (int o = 0; o < 4; ++o) {
-                        if (r == 0)
-                            s[o] = d2{0.0, 0.0};
-                        mac(s[o], x, kb[bt % KB][rr * 4 + o]);
-                    }
-                }
-                if (bt % NRB == NRB - 1)
+                    d2 x[H];
+                    points(bt * KR + rr, x);
 #pragma unroll
                     for (int o = 0; o < 4; ++o)
-                        rows[o * ROW + j] = s[o];
+#pragma unroll
+                        for (int q = 0; q < H; ++q)
+                            mac(s[o][q], x[q],
+                                kb[bt % KB][(rr * 4 + o) * H + q]);
+                }
             }
         } else {
-            const d2 *kp = reinterpret_cast<const d2 *>(key) +
-                           (size_t)i * R * 4 * M;
-            for (int j = tid; j < M; j += T) {
-                d2 s[4] = {};
-                for (int r = 0; r < R; ++r) {
-                    const d2 x = rows[r * ROW + j];
-#pragma unroll
-                    for (int o = 0; o < 4; ++o)
-                        mac(s[o], x, kp[(r * 4 + o) * M + j]);
-                }
+            const d2 *kp = kpt + (size_t)i * R * 4 * M;
+            for (int r = 0; r < R; ++r) {
+                d2 x[H];
+                points(r, x);
 #pragma unroll
                 for (int o = 0; o < 4; ++o)
-                    rows[o * ROW + j] = s[o];
+#pragma unroll
+                    for (int q = 0; q < H; ++q)
+                        mac(s[o][q], x[q], kp[((r * 4 + o) * H + q) * MS]);
             }
+        }
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+            if constexpr (H == 2)
+                bf_inv<false>(s[o][0], s[o][H - 1], xs);
+#pragma unroll
+            for (int q = 0; q < H; ++q)
+                rows[(o * H + q) * ROW + tid] = s[o][q];
         }
         fft_barrier();
         // (3) inverse transforms; the sums are integers below 2^51, so
         // adding 1.5 * 2^52 leaves them rounded in the low mantissa bits
         if constexpr (ROLE == 3)
             key_issue(min(i_nxt, n - 1), 0, kb[0], 0, KL);
-        for (int t0 = wave * FPW; ROLE != 3 && t0 < 4;
+        for (int t0 = wave * FPW; ROLE != 3 && t0 < ni;
              t0 += C::WAVES * FPW) {
-            const int o = FPW == 1 ? t0 : t0 + f;
-            if (FPW > 1 && o >= 4)
+            const int oq = FPW == 1 ? t0 : t0 + f;   // output, parity
+            if (FPW > 1 && oq >= ni)
                 break;
-            d2 *row = rows + o * ROW;
+            d2 *row = rows + oq * ROW;
             d2 v[PPL];
 #pragma unroll
             for (int k = 0; k < PPL; ++k)
                 v[k] = row[k * LPF + lf];
-            fft_inverse<N>(v, row, lf, tw);
-            uint32_t *ao = acc + (o >> 1) * N + lf;
+            fft_inverse<N>(v, row, lf, tw, [&](int m) {
+                if constexpr (ROLE == 4)
+                    key_issue(min(i_nxt, n - 1), 0, kb[0], m * KL / 4,
+                              (m + 1) * KL / 4);
+            });
+            const int o = oq / H;
+            uint32_t *ao = acc + (o >> 1) * N + oq % H * M + lf;
             const int hs = 16 * (o & 1);
 #pragma unroll
             for (int k = 0; k < PPL; ++k) {
@@ -592,19 +645,21 @@ void k_bootstrap_fft(
                     (uint32_t)__double_as_longlong(v[k].y + magic) << hs;
                 __hip_atomic_fetch_add(ao + k * LPF, re, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
-                __hip_atomic_fetch_add(ao + k * LPF + M, im, __ATOMIC_RELAXED,
+                __hip_atomic_fetch_add(ao + k * LPF + MS, im, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             if (ROLE)
-                t0 = 4;
+                t0 = ni;
         }
         i = i_nxt;
     }
     };
     if constexpr (AHEAD) {
-        if (fw < 0)
+        if constexpr (2 * L * H >= C::WAVES && 4 * H >= C::WAVES)
+            steps(std::integral_constant<int, 4>{});
+        else if (fw < 0)
             steps(std::integral_constant<int, 1>{});
-        else if (wave < 4)
+        else if (wave < ni)
             steps(std::integral_constant<int, 2>{});
         else
             steps(std::integral_constant<int, 3>{});
@@ -620,7 +675,7 @@ void k_bootstrap_fft(
         if (j == 0)
             v = acc[0];
         else if (j < N)
-            v = 0u - acc[N - j];
+            v = 0u - acc[aidx(N - j)];
         else
             v = acc[N];
         o[j] = v;
@@ -667,12 +722,22 @@ template <int N> std::vector<double> fft_table()
             const unsigned pre = ((unsigned)f << C::BS) | (unsigned)bl;
             push_twiddles(t, rev_bits(pre, 2 * C::RB), 2 * C::RB, C::LAST);
         }
+    if (C::H == 2)
+        for (int j = 0; j < C::MS; ++j) {
+            // the root of register j / LPF of lane j mod LPF
+            const unsigned pre = (unsigned)(j % C::LPF * C::PPL + j / C::LPF);
+            push_twiddles(t, rev_bits(pre, C::LOGM), C::LOGM, 1);
+        }
     return t;
 }
 
-// Rows of a key batch (L > 0): one point's whole column, a step ahead, at
-// N = 1024; two rows elsewhere.  Two waves per SIMD: 256 registers.
-template <int N> constexpr int FKR(int L) { return N == 1024 ? 2 * L : 2; }
+// Rows of a key batch (L > 0): the whole column at N = 1024, and at N = 2048
+// where it fits the registers; two rows elsewhere.  Two waves per SIMD: 256
+// registers.
+template <int N> constexpr int FKR(int L)
+{
+    return N == 1024 || (N == 2048 && L == 2) ? 2 * L : 2;
+}
 constexpr int FWPE = 2;
 
 template <int N, int L, int KR> int fft_attr1()
