@@ -359,19 +359,37 @@ size_t fft_smem(int N, int l)
                        : fft_smem_n<2048>(l);
 }
 
-// L (gadget levels) is a compile-time constant for the sets in use, 0 reads
-// it at run time.  A thread reads the key values of its slot (H points) KR
-// digit rows at a time, a batch ahead of their use (the first batch before
-// the barrier); KR = 2L holds the whole column, read during the transforms.
+// The bootstraps [*from, *to) a launch of NB per workgroup takes of a batch
+// of `count`.  pair_width > 0: the batch is split between a launch of two
+// per workgroup, which takes whole rounds of pair_width and a last one of
+// more than half, and a launch of one per workgroup for the rest.
+__device__ __forceinline__ void fft_share(int NB, int count, int pair_width,
+                                          int *from, int *to)
+{
+    *from = 0;
+    *to = count;
+    if (pair_width > 0) {
+        const int rest = count % pair_width;
+        const int cut = 2 * rest > pair_width ? count : count - rest;
+        *(NB == 2 ? to : from) = cut;
+    }
+}
+
+// NB: bootstraps per workgroup (they share the key values).  L (gadget
+// levels) is a compile-time constant for the sets in use, 0 reads it at run
+// time.  A thread reads the key values of its slot (H points) KR digit rows
+// at a time, a batch ahead of their use (the first batch before the
+// barrier); KR = 2L holds the whole column, read during the transforms.
 // WPE: waves per SIMD the registers are budgeted for.
-template <int N, int L, int KR, int WPE>
+template <int N, int NB, int L, int KR, int WPE>
 __global__ __launch_bounds__(FCfg<N>::THREADS)
 __attribute__((amdgpu_waves_per_eu(WPE)))
 void k_bootstrap_fft(
     const double *__restrict__ key, const double *__restrict__ tab,
     const uint32_t *__restrict__ in, const uint32_t *__restrict__ testv,
     uint32_t *__restrict__ out, int B, const int32_t *__restrict__ d_count,
-    const uint32_t *__restrict__ stop, int stop_cap, int n, int beta, int l_rt)
+    int pair_width, const uint32_t *__restrict__ stop, int stop_cap, int n,
+    int beta, int l_rt)
 {
     using C = FCfg<N>;
     constexpr int M = C::M, PPL = C::PPL, LPF = C::LPF, FPW = C::FPW;
@@ -380,15 +398,18 @@ void k_bootstrap_fft(
     constexpr int LOG2_2N = __builtin_ctz(2 * N);
     const int l = L ? L : l_rt;
     const int R = 2 * l;
+    const int RB = (R > 4 ? R : 4) * H;          // rows of a bootstrap
     extern __shared__ __align__(16) unsigned char smem[];
-    d2 *rows = reinterpret_cast<d2 *>(smem);
-    uint32_t *acc = reinterpret_cast<uint32_t *>(rows + (R > 4 ? R : 4) * H * ROW);
+    d2 *rows = reinterpret_cast<d2 *>(smem);     // [NB][RB][ROW]
+    uint32_t *acc = reinterpret_cast<uint32_t *>(rows + NB * RB * ROW);
     // accumulator word of coefficient t of a component
     auto aidx = [](int t) { return H == 2 ? (t & 1) * M + (t >> 1) : t; };
 
     const int count = d_count ? min(B, *d_count) : B;
-    const int g = blockIdx.x;
-    if (g >= count)
+    int from, to;
+    fft_share(NB, count, pair_width, &from, &to);
+    const int g0 = from + blockIdx.x * NB;
+    if (g0 >= to)
         return;
     // narrow INT8 batches are refused while the latency-mode error word is
     // set (cggi_ctx_latency_abort)
@@ -397,11 +418,17 @@ void k_bootstrap_fft(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lf = lane % LPF, f = lane / LPF;
-    const uint32_t *ct = in + (size_t)g * (n + 1);
+    // (a last workgroup with fewer than NB bootstraps repeats its last one)
+    const uint32_t *ct[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+        ct[b] = in + (size_t)min(g0 + b, to - 1) * (n + 1);
 
     // ACC = (0, X^(2N - b~) * v)
-    {
-        const int e = (2 * N - (int)fft_modswitch(ct[n], LOG2_2N)) & (2 * N - 1);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int e = (2 * N - (int)fft_modswitch(ct[b][n], LOG2_2N)) &
+                      (2 * N - 1);
         for (int m = tid; m < N; m += T) {
             uint32_t v = testv ? testv[m] : (1u << 29);
             int t = m + e;
@@ -411,8 +438,8 @@ void k_bootstrap_fft(
                 t -= N;
                 v = 0u - v;
             }
-            acc[aidx(t)] = 0u;
-            acc[N + aidx(t)] = v;
+            acc[2 * N * b + aidx(t)] = 0u;
+            acc[2 * N * b + N + aidx(t)] = v;
         }
     }
     Tw<N> tw;
@@ -437,16 +464,22 @@ void k_bootstrap_fft(
     constexpr int NBT = L ? 2 * L / (KR ? KR : 1) : 1;
     constexpr int KB = L ? (AHEAD ? 1 : 2) : 1, KL = L ? KR * 4 * H : 1;
     d2 kb[KB][KL];
-    const d2 *kpt = reinterpret_cast<const d2 *>(key) + tid;
+    const d2 *key2 = reinterpret_cast<const d2 *>(key);
     auto key_issue = [&](int i, int bt, d2 (&dst)[KL], int q0, int q1) {
-        const d2 *src = kpt + ((size_t)i * R + bt * KR) * 4 * M;
+        // buffer loads: the row's offset is scalar and the lane's offset the
+        // same for every row, so a load takes no vector address arithmetic
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<d2 *>(key2 + (size_t)i * R * 4 * M), 0, R * 4 * M * 16,
+            0x00020000);
 #pragma unroll
         for (int q = q0; q < q1; ++q)
-            dst[q] = src[q * MS];
+            dst[q] = __builtin_bit_cast(
+                d2, __builtin_amdgcn_raw_buffer_load_b128(
+                        rsrc, tid * 16, (bt * KL + q) * MS * 16, 0));
         __builtin_amdgcn_sched_barrier(0);
     };
     // forward transforms run on the last waves, inverse ones on the first
-    const int nf = R * H, ni = 4 * H;
+    const int nf = NB * R * H, ni = NB * 4 * H;
     const int fw = wave - (C::WAVES * FPW > nf ? C::WAVES - (nf + FPW - 1) / FPW
                                                : 0);
 
@@ -460,7 +493,7 @@ void k_bootstrap_fft(
     // would hold up phase (1)).
     auto steps = [&](auto role_c) {
     constexpr int ROLE = decltype(role_c)::value;   // 0: any wave
-    uint32_t ev = 0;                // rotations of 64 steps, one per lane
+    uint32_t ev[NB] = {};           // rotations of 64 steps, one per lane
     unsigned long long live = 0;    // those still to come, nonzero ones
     int i0 = -64;                   // first step of the 64
     auto next = [&]() -> int {
@@ -468,8 +501,13 @@ void k_bootstrap_fft(
             i0 += 64;
             if (i0 >= n)
                 return n;
-            ev = fft_modswitch(ct[min(i0 + lane, n)], LOG2_2N) & (2 * N - 1);
-            live = __ballot(ev != 0 && i0 + lane < n);
+            uint32_t any = 0;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                ev[b] = fft_modswitch(ct[b][min(i0 + lane, n)], LOG2_2N);
+                any |= ev[b];
+            }
+            live = __ballot(any != 0 && i0 + lane < n);
         }
         const int b = __builtin_ctzll(live);
         live &= live - 1;
@@ -480,16 +518,19 @@ void k_bootstrap_fft(
         if (i < n)
             key_issue(i, 0, kb[0], 0, ROLE == 3 ? KL : KL / 2);
     while (i < n) {
-        const int e = __builtin_amdgcn_readlane(ev, i & 63);
+        int e[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            e[b] = __builtin_amdgcn_readlane(ev[b], i & 63);
         const int i_nxt = next();
         fft_barrier();   // ACC of the previous step complete
         // (0) digits of X^e ACC - ACC: those of coefficients j and j + M of
         // polynomial r side by side in dword j / H of row (r, j mod H),
         // whose transform's wave alone reads them
         {
-            constexpr int ITEMS = 2 * H;
+            constexpr int ITEMS = NB * 2 * H;
             uint32_t x[ITEMS][2], y[ITEMS][2];
-            // item it: component it / H, coefficients j and j + M
+            // item it: bootstrap and component it / H, coefficients j, j + M
             auto coef = [&](int it) { return H * tid + it % H; };
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it)
@@ -497,24 +538,25 @@ void k_bootstrap_fft(
                 for (int q = 0; q < 2; ++q) {
                     const int t = coef(it) + q * M;
                     const uint32_t *ac = acc + it / H * N;
-                    x[it][q] = ac[aidx((t - e) & (N - 1))];
+                    x[it][q] = ac[aidx((t - e[it / (2 * H)]) & (N - 1))];
                     y[it][q] = ac[aidx(t)];
                 }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
+                const int b = it / (2 * H), c = it / H % 2;
                 uint32_t w[2];
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
                     // all ones where the rotated index wrapped (bit N)
                     const uint32_t mk = (uint32_t)__builtin_amdgcn_sbfe(
-                        coef(it) + q * M - e, LOG2_2N - 1, 1);
+                        coef(it) + q * M - e[b], LOG2_2N - 1, 1);
                     w[q] = ((x[it][q] ^ mk) + (dig_off - y[it][q] - mk)) ^
                            dig_flip;
                 }
-                uint32_t *dr = reinterpret_cast<uint32_t *>(
-                                   rows + (it / H * l * H + it % H) * ROW) +
-                               tid;
+                uint32_t *dr =
+                    reinterpret_cast<uint32_t *>(
+                        rows + (b * RB + c * l * H + it % H) * ROW) + tid;
 #pragma unroll
                 for (int p = 0; p < (L ? L : l); ++p) {
                     const int sh = 32 - (p + 1) * beta;
@@ -529,12 +571,12 @@ void k_bootstrap_fft(
         // (1) their transforms
         if constexpr (ROLE == 1)
             key_issue(i, 0, kb[0], 0, KL);
-        for (int t0 = fw * FPW; ROLE != 1 && t0 >= 0 && t0 < nf;
-             t0 += C::WAVES * FPW) {
+        auto forward = [&](int t0, auto mid) {
             // surplus lanes repeat the last polynomial's work (the same
             // stores of the same values)
             const int pol = FPW == 1 ? t0 : min(t0 + f, nf - 1);
-            d2 *row = rows + pol * ROW;
+            const int rh = R * H;
+            d2 *row = rows + (NB == 1 ? pol : pol / rh * RB + pol % rh) * ROW;
             const uint32_t *dr = reinterpret_cast<const uint32_t *>(row) + lf;
             uint32_t dg[PPL];
 #pragma unroll
@@ -546,17 +588,24 @@ void k_bootstrap_fft(
                 v[k].x = (double)(int16_t)dg[k];
                 v[k].y = (double)((int32_t)dg[k] >> 16);
             }
-            fft_forward<N>(v, row, lf, tw, [&](int m) {
-                if constexpr (ROLE == 2)
-                    key_issue(i, 0, kb[0], m * KL / 2, (m + 1) * KL / 2);
-                if constexpr (ROLE == 4)
-                    key_issue(i, 0, kb[0], (m + 2) * KL / 4, (m + 3) * KL / 4);
-            });
-            if (ROLE)           // one transform per wave
-                t0 = nf;
+            fft_forward<N>(v, row, lf, tw, mid);
 #pragma unroll
             for (int k = 0; k < PPL; ++k)
                 row[k * LPF + lf] = v[k];
+        };
+        if constexpr (ROLE == 2 || ROLE == 4) {
+            forward(fw, [&](int m) {
+                key_issue(i, 0, kb[0],
+                          ROLE == 2 ? m * KL / 2 : (m + 2) * KL / 4,
+                          ROLE == 2 ? (m + 1) * KL / 2 : (m + 3) * KL / 4);
+            });
+            for (int t0 = fw + C::WAVES; t0 < nf; t0 += C::WAVES)
+                forward(t0, [](int) {});
+        } else if constexpr (ROLE == 3) {
+            forward(fw, [](int) {});
+        } else if constexpr (ROLE == 0) {
+            for (int t0 = fw * FPW; t0 >= 0 && t0 < nf; t0 += C::WAVES * FPW)
+                forward(t0, [](int) {});
         }
         if constexpr (L && !AHEAD)
             key_issue(i, 0, kb[0], 0, KL);
@@ -568,51 +617,58 @@ void k_bootstrap_fft(
             s.y = fma(x.x, k.y, fma(x.y, k.x, s.y));
         };
         // a row's points in the thread's slot
-        auto points = [&](int r, d2 (&x)[H]) {
+        auto points = [&](int row, d2 (&x)[H]) {
 #pragma unroll
             for (int q = 0; q < H; ++q)
-                x[q] = rows[(r * H + q) * ROW + tid];
+                x[q] = rows[(row + q) * ROW + tid];
             if constexpr (H == 2)
                 bf_fwd<false>(x[0], x[H - 1], xs);
         };
-        d2 s[4][H] = {};
+        d2 s[NB][4][H] = {};
         if constexpr (L > 0) {
 #pragma unroll
             for (int bt = 0; bt < NBT; ++bt) {
                 if (bt + 1 < NBT)
                     key_issue(i, bt + 1, kb[(bt + 1) % KB], 0, KL);
 #pragma unroll
-                for (int rr = 0; rr < KR; ++rr) {
+                for (int rr = 0; rr < KR; ++rr)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        d2 x[H];
+                        points(b * RB + (bt * KR + rr) * H, x);
+#pragma unroll
+                        for (int o = 0; o < 4; ++o)
+#pragma unroll
+                            for (int q = 0; q < H; ++q)
+                                mac(s[b][o][q], x[q],
+                                    kb[bt % KB][(rr * 4 + o) * H + q]);
+                    }
+            }
+        } else {
+            const d2 *kp = key2 + (size_t)i * R * 4 * M + tid;
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
                     d2 x[H];
-                    points(bt * KR + rr, x);
+                    points(b * RB + r * H, x);
 #pragma unroll
                     for (int o = 0; o < 4; ++o)
 #pragma unroll
                         for (int q = 0; q < H; ++q)
-                            mac(s[o][q], x[q],
-                                kb[bt % KB][(rr * 4 + o) * H + q]);
+                            mac(s[b][o][q], x[q],
+                                kp[((r * 4 + o) * H + q) * MS]);
                 }
-            }
-        } else {
-            const d2 *kp = kpt + (size_t)i * R * 4 * M;
-            for (int r = 0; r < R; ++r) {
-                d2 x[H];
-                points(r, x);
-#pragma unroll
-                for (int o = 0; o < 4; ++o)
-#pragma unroll
-                    for (int q = 0; q < H; ++q)
-                        mac(s[o][q], x[q], kp[((r * 4 + o) * H + q) * MS]);
-            }
         }
 #pragma unroll
-        for (int o = 0; o < 4; ++o) {
-            if constexpr (H == 2)
-                bf_inv<false>(s[o][0], s[o][H - 1], xs);
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int q = 0; q < H; ++q)
-                rows[(o * H + q) * ROW + tid] = s[o][q];
-        }
+            for (int o = 0; o < 4; ++o) {
+                if constexpr (H == 2)
+                    bf_inv<false>(s[b][o][0], s[b][o][H - 1], xs);
+#pragma unroll
+                for (int q = 0; q < H; ++q)
+                    rows[(b * RB + o * H + q) * ROW + tid] = s[b][o][q];
+            }
         fft_barrier();
         // (3) inverse transforms; the sums are integers below 2^51, so
         // adding 1.5 * 2^52 leaves them rounded in the low mantissa bits
@@ -620,10 +676,12 @@ void k_bootstrap_fft(
             key_issue(min(i_nxt, n - 1), 0, kb[0], 0, KL);
         for (int t0 = wave * FPW; ROLE != 3 && t0 < ni;
              t0 += C::WAVES * FPW) {
-            const int oq = FPW == 1 ? t0 : t0 + f;   // output, parity
-            if (FPW > 1 && oq >= ni)
+            // bootstrap, output, parity
+            const int boq = FPW == 1 ? t0 : t0 + f;
+            if (FPW > 1 && boq >= ni)
                 break;
-            d2 *row = rows + oq * ROW;
+            const int b = NB == 1 ? 0 : boq / (4 * H), oq = boq - b * 4 * H;
+            d2 *row = rows + (b * RB + oq) * ROW;
             d2 v[PPL];
 #pragma unroll
             for (int k = 0; k < PPL; ++k)
@@ -634,7 +692,7 @@ void k_bootstrap_fft(
                               (m + 1) * KL / 4);
             });
             const int o = oq / H;
-            uint32_t *ao = acc + (o >> 1) * N + oq % H * M + lf;
+            uint32_t *ao = acc + (2 * b + (o >> 1)) * N + oq % H * M + lf;
             const int hs = 16 * (o & 1);
 #pragma unroll
             for (int k = 0; k < PPL; ++k) {
@@ -655,7 +713,7 @@ void k_bootstrap_fft(
     }
     };
     if constexpr (AHEAD) {
-        if constexpr (2 * L * H >= C::WAVES && 4 * H >= C::WAVES)
+        if constexpr (NB * 2 * L * H >= C::WAVES && NB * 4 * H >= C::WAVES)
             steps(std::integral_constant<int, 4>{});
         else if (fw < 0)
             steps(std::integral_constant<int, 1>{});
@@ -669,16 +727,22 @@ void k_bootstrap_fft(
     __syncthreads();
 
     // sample extraction of coefficient 0
-    uint32_t *o = out + (size_t)g * (N + 1);
-    for (int j = tid; j <= N; j += T) {
-        uint32_t v;
-        if (j == 0)
-            v = acc[0];
-        else if (j < N)
-            v = 0u - acc[aidx(N - j)];
-        else
-            v = acc[N];
-        o[j] = v;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if (g0 + b >= to)
+            break;
+        uint32_t *o = out + (size_t)(g0 + b) * (N + 1);
+        const uint32_t *ac = acc + 2 * N * b;
+        for (int j = tid; j <= N; j += T) {
+            uint32_t v;
+            if (j == 0)
+                v = ac[0];
+            else if (j < N)
+                v = 0u - ac[aidx(N - j)];
+            else
+                v = ac[N];
+            o[j] = v;
+        }
     }
 }
 
@@ -740,19 +804,25 @@ template <int N> constexpr int FKR(int L)
 }
 constexpr int FWPE = 2;
 
-template <int N, int L, int KR> int fft_attr1()
+// Two bootstraps per workgroup (N = 1024, l = 2 or 3, LDS permitting).
+template <int N> constexpr bool FPAIR(int L) { return N == 1024 && L > 0; }
+
+template <int N, int NB, int L, int KR> int fft_attr1()
 {
     CGGI_HIP_TRY(hipFuncSetAttribute(
-        reinterpret_cast<const void *>(&k_bootstrap_fft<N, L, KR, FWPE>),
+        reinterpret_cast<const void *>(&k_bootstrap_fft<N, NB, L, KR, FWPE>),
         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
     return CGGI_OK;
 }
 
-template <int N> int fft_attr(int l)
+template <int N, int L> int fft_attr()
 {
-    return l == 3   ? fft_attr1<N, 3, FKR<N>(3)>()
-           : l == 2 ? fft_attr1<N, 2, FKR<N>(2)>()
-                    : fft_attr1<N, 0, 0>();
+    constexpr int KR = L ? FKR<N>(L) : 0;
+    int rc = fft_attr1<N, 1, L, KR>();
+    if constexpr (FPAIR<N>(L))
+        if (!rc)
+            rc = fft_attr1<N, 2, L, KR>();
+    return rc;
 }
 
 template <int N> int fft_key_t(Ctx *c, const uint32_t *bsk, hipStream_t s)
@@ -775,7 +845,47 @@ template <int N> int fft_key_t(Ctx *c, const uint32_t *bsk, hipStream_t s)
     hipLaunchKernelGGL(k_fft_key<N>, dim3((npoly + C::FPW - 1) / C::FPW),
                        dim3(64), 0, s, bsk, c->fft_tw, c->bsk_fft, npoly);
     CGGI_HIP_TRY(hipGetLastError());
-    return fft_attr<N>(sh.l);
+    return sh.l == 3   ? fft_attr<N, 3>()
+           : sh.l == 2 ? fft_attr<N, 2>()
+                       : fft_attr<N, 0>();
+}
+
+template <int N, int L>
+int fft_launch_l(const Ctx *c, const uint32_t *in, const uint32_t *testv,
+                 uint32_t *out, int B, const int32_t *d_count,
+                 const uint32_t *stop, int stop_cap, hipStream_t s)
+{
+    const Shape &sh = c->sh;
+    constexpr int KR = L ? FKR<N>(L) : 0;
+    const size_t smem = fft_smem(N, sh.l);
+    int pair_width = 0, grid = B;
+    if constexpr (FPAIR<N>(L)) {
+        // Batches wider than the chip: two bootstraps per workgroup in
+        // rounds of twice the CUs, one per workgroup for a rest of at most
+        // half a round (and for every narrower batch: a step of two takes
+        // 1.4 times a step of one).  A count read on the device is split
+        // there, so both are launched; the one with no share exits at once.
+        pair_width = 2 * c->cus;
+        grid = B < c->cus ? B : c->cus;
+        const int rest = B % pair_width;
+        const bool pairs = B > c->cus, ones = d_count || (rest && rest <= c->cus);
+        if (pairs) {
+            hipLaunchKernelGGL((k_bootstrap_fft<N, 2, L, KR, FWPE>),
+                               dim3((B + 1) / 2), dim3(FCfg<N>::THREADS),
+                               2 * smem, s, c->bsk_fft, c->fft_tw, in, testv,
+                               out, B, d_count, pair_width, stop, stop_cap,
+                               sh.n, sh.beta, sh.l);
+            CGGI_HIP_TRY(hipGetLastError());
+        }
+        if (!ones)
+            return CGGI_OK;
+    }
+    hipLaunchKernelGGL((k_bootstrap_fft<N, 1, L, KR, FWPE>), dim3(grid),
+                       dim3(FCfg<N>::THREADS), smem, s, c->bsk_fft,
+                       c->fft_tw, in, testv, out, B, d_count, pair_width, stop,
+                       stop_cap, sh.n, sh.beta, sh.l);
+    CGGI_HIP_TRY(hipGetLastError());
+    return CGGI_OK;
 }
 
 template <int N>
@@ -783,22 +893,14 @@ int fft_launch(const Ctx *c, const uint32_t *in, const uint32_t *testv,
                uint32_t *out, int B, const int32_t *d_count,
                const uint32_t *stop, int stop_cap, hipStream_t s)
 {
-    const Shape &sh = c->sh;
-    const size_t smem = fft_smem(N, sh.l);
-#define FFT_LAUNCH(LL, KR, WPE)                                              \
-    hipLaunchKernelGGL((k_bootstrap_fft<N, LL, KR, WPE>), dim3(B),           \
-                       dim3(FCfg<N>::THREADS), smem, s, c->bsk_fft,          \
-                       c->fft_tw, in, testv, out, B, d_count, stop,          \
-                       stop_cap, sh.n, sh.beta, sh.l)
-    if (sh.l == 3)
-        FFT_LAUNCH(3, FKR<N>(3), FWPE);
-    else if (sh.l == 2)
-        FFT_LAUNCH(2, FKR<N>(2), FWPE);
-    else
-        FFT_LAUNCH(0, 0, FWPE);
-#undef FFT_LAUNCH
-    CGGI_HIP_TRY(hipGetLastError());
-    return CGGI_OK;
+    return c->sh.l == 3
+               ? fft_launch_l<N, 3>(c, in, testv, out, B, d_count, stop,
+                                    stop_cap, s)
+           : c->sh.l == 2
+               ? fft_launch_l<N, 2>(c, in, testv, out, B, d_count, stop,
+                                    stop_cap, s)
+               : fft_launch_l<N, 0>(c, in, testv, out, B, d_count, stop,
+                                    stop_cap, s);
 }
 
 } // namespace
