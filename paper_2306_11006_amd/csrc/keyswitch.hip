@@ -174,9 +174,7 @@ __global__ __launch_bounds__(KS_THREADS) void k_keyswitch(
 typedef int ks_v4i __attribute__((ext_vector_type(4)));
 typedef int ks_v16i __attribute__((ext_vector_type(16)));
 
-constexpr int KSM_ITEMS = 64;   // ciphertexts per workgroup (2 row tiles)
-constexpr int KSM_WAVES = 8;    // most column tiles per workgroup (1 / wave)
-constexpr int KSM_JMAX = 256;   // most j per workgroup (LDS: 64 KB of a')
+constexpr int KSM_THREADS = 512;   // eight waves
 
 // ksk [N][t][2^gamma][n+1] -> limb blocks [NT][N][KSJ][4][64 lanes][16 B]:
 // byte e of lane l in block (nt, j, sj, q) is limb q of
@@ -243,136 +241,272 @@ __global__ __launch_bounds__(256) void k_ks_init(const uint32_t *__restrict__ in
     }
 }
 
-// One workgroup: KSM_ITEMS ciphertexts x (one 32-column tile per wave) x
-// one range of j; each wave holds 2 row tiles x 4 limbs accumulators, reads
-// its key blocks two K-steps ahead, builds the one-hot digits from a' in
-// LDS, and subtracts its recombined partial sums from the output rows with
-// device atomics (mod 2^32, so the order of the j ranges does not matter).
-template <bool LEVEL>
-__global__ __launch_bounds__(64 * KSM_WAVES) void k_ks_mfma(
+// One workgroup of eight waves: 32 RT ciphertexts (RT row tiles) x one range
+// of j x 8 UW column units, UW = 8 / RT per wave; a unit is one limb of a
+// 32-column tile, so a wave holds RT x UW = 8 accumulators.
+//  * The one-hot digits (A) are the same for every column: each thread builds
+//    the slots of one (ciphertext, j) of a chunk of 512 / (32 RT) j, and the
+//    waves read them from LDS, double-buffered by chunk (one barrier per
+//    chunk).
+//  * A wave reads its key blocks (B) from L2 PF K-steps ahead, UW KB per
+//    eight MFMAs.  With RT = 4 that is 32 bytes a cycle and CU, half the
+//    vector cache's rate; 64 ciphertexts with one tile per wave and the
+//    digits built by every wave ran at that rate: 185 -> 103 us for 1024
+//    default ciphertexts, 2.75 -> 1.13 ms for 16,384 (2.4 POP/s of int8
+//    work, near what the matrix cores sustain at the power limit), 0.68 ->
+//    0.46 ms for 1024 large ones.
+//  * The recombined limb sums are subtracted from the output rows with device
+//    atomics (mod 2^32, so the order of the j ranges does not matter); with
+//    RT = 4 a tile's two waves add theirs in LDS first.
+// KSJ: K-steps per j as a constant (the chunk's loop unrolls and the loads in
+// flight can be counted), 0 any number, -1 any number at base 2 (two levels
+// per dword of slots).
+template <int RT, bool LEVEL, int KSJ>
+__global__ __launch_bounds__(KSM_THREADS) void k_ks_mfma(
     const int8_t *__restrict__ kski8, const uint32_t *__restrict__ in,
     uint32_t *__restrict__ out, int B, KsLevel lv, int n, int N, int gamma,
-    int t, int ksj, int nt_tiles, int jchunk)
+    int t, int ksj_rt, int nt_tiles, int jchunk)
 {
-    __shared__ uint32_t a_l[KSM_ITEMS * KSM_JMAX];
-    __shared__ uint32_t *dst_l[KSM_ITEMS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int it0 = blockIdx.x * KSM_ITEMS;
-    const int nt = blockIdx.y * (blockDim.x >> 6) + wave;
+    constexpr bool BASE2 = KSJ < 0;
+    const int ksj = KSJ > 0 ? KSJ : ksj_rt;
+    constexpr int UW = 8 / RT, ROWS = 32 * RT, CJ = KSM_THREADS / ROWS;
+    // pad slots per j: the 16 / CJ rows x CJ j that 16 lanes build at once
+    // then fall in distinct banks
+    constexpr int PADJ = 16 / CJ;
+    extern __shared__ __align__(16) unsigned char ks_smem[];
+    __shared__ uint32_t *dst_l[ROWS];
+    // A: [buffer][chunk j][K-step of j][row tile][kappa half][32 rows][16 B],
+    // PADJ slots after each j
+    ks_v4i *al = reinterpret_cast<ks_v4i *>(ks_smem);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int unit = (blockIdx.y * 8 + wave) * UW;
+    const int nt = unit >> 2, q0 = unit & 3;
     const int j0 = blockIdx.z * jchunk;
-    const int JC = min(N, j0 + jchunk) - j0;
+    const int JC = min(N, j0 + jchunk) - j0;      // a multiple of CJ
+    const int base = 1 << gamma;
     const uint32_t round_off = (t * gamma < 32) ? 1u << (31 - t * gamma) : 0u;
-    for (int m = threadIdx.x; m < KSM_ITEMS; m += blockDim.x) {
-        const uint32_t *src0, *src1;
-        uint32_t *dst;
-        ks_item<LEVEL>(it0 + m, B, in, out, lv, n, N, src0, src1, dst);
-        dst_l[m] = dst;
-    }
-    for (int idx = threadIdx.x; idx < KSM_ITEMS * JC; idx += blockDim.x) {
-        const int m = idx / JC, jj = idx - m * JC;
-        const uint32_t *src0, *src1;
-        uint32_t *dst;
-        uint32_t a = 0;
-        if (ks_item<LEVEL>(it0 + m, B, in, out, lv, n, N, src0, src1, dst)) {
-            a = src0[j0 + jj];
-            if (src1)
-                a += src1[j0 + jj];
-        }
-        a_l[m * KSM_JMAX + jj] = a + round_off;
-    }
-    __syncthreads();
-    if (nt >= nt_tiles || JC <= 0)
-        return;
 
-    const int base = 1 << gamma, kh = lane >> 5, r = lane & 31;
-    const int S = JC * ksj;              // K-steps of this workgroup
-    const int8_t *bp = kski8 + ((size_t)nt * N + j0) * ksj * 4096 + lane * 16;
-    auto loadb = [&](int s, ks_v4i (&dst)[4]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            dst[q] = *reinterpret_cast<const ks_v4i *>(bp + (size_t)s * 4096 +
-                                                       q * 1024);
+    // this thread's ciphertext and j of a chunk
+    const int row = threadIdx.x / CJ, jj = threadIdx.x % CJ;
+    const uint32_t *src0, *src1;
+    uint32_t *dst;
+    const bool live = ks_item<LEVEL>(blockIdx.x * ROWS + row, B, in, out, lv, n,
+                                     N, src0, src1, dst);
+    if (jj == 0)
+        dst_l[row] = dst;
+    // (always loads, from row 0 where there is no ciphertext: a load under a
+    // condition would make the wait for it one for every load in flight)
+    const bool second = LEVEL && src1;
+    if (!live)
+        src0 = LEVEL ? lv.big : in;
+    if (!second)
+        src1 = src0;
+    struct Pair {
+        uint32_t a, b;
     };
-    // the lane's 16 one-hot bytes of K-step slot block sj for a' + offset u
-    auto onehot = [&](uint32_t u, int sj) {
-        ks_v4i a;
+    auto load_u = [&](int c) -> Pair {
+        const int j = j0 + min(c * CJ, JC - CJ) + jj;
+        return {src0[j], LEVEL ? src1[j] : 0u};
+    };
+    // the slots of this thread's (ciphertext, j), without branches
+    auto build = [&](int buf, Pair uu) {
+        const uint32_t u = uu.a + (second ? uu.b : 0u) + round_off;
+        ks_v4i *d = al + (buf * CJ + jj) * (ksj * RT * 64 + PADJ) +
+                    (row >> 5) * 64 + (row & 31);
+        for (int sj = 0; sj < ksj; ++sj) {
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const int slot0 = 32 * sj + 16 * kh + 4 * w;
-            uint32_t word = 0;
-            if (base >= 4) {
-                const int p = slot0 >> gamma;
-                if (p < t) {
-                    const uint32_t d = (u >> (32 - (p + 1) * gamma)) &
-                                       (uint32_t)(base - 1);
-                    const uint32_t rel = d - (uint32_t)(slot0 & (base - 1));
-                    word = rel < 4u ? 1u << (8 * rel) : 0u;
-                }
-            } else {                       // base 2: two levels per dword
+            for (int kh = 0; kh < 2; ++kh) {
+                ks_v4i a;
 #pragma unroll
-                for (int hp = 0; hp < 2; ++hp) {
-                    const int p = (slot0 >> 1) + hp;
-                    if (p < t) {
-                        const uint32_t d = (u >> (31 - p)) & 1u;
-                        word |= 1u << (8 * (2 * hp + (int)d));
+                for (int w = 0; w < 4; ++w) {
+                    const int slot0 = 32 * sj + 16 * kh + 4 * w;
+                    uint32_t word = 0;
+                    if (!BASE2) {
+                        const int p = slot0 >> gamma;
+                        const uint32_t dg =
+                            (u >> ((32 - (p + 1) * gamma) & 31)) &
+                            (uint32_t)(base - 1);
+                        const uint32_t rel =
+                            dg - (uint32_t)(slot0 & (base - 1));
+                        word = (rel < 4u ? 1u << (8 * (rel & 3)) : 0u) &
+                               (uint32_t)((p - t) >> 31);
+                    } else {
+#pragma unroll
+                        for (int hp = 0; hp < 2; ++hp) {
+                            const int p = (slot0 >> 1) + hp;
+                            const uint32_t dg = (u >> ((31 - p) & 31)) & 1u;
+                            word |= (1u << (8 * (2 * hp + (int)dg))) &
+                                    (uint32_t)((p - t) >> 31);
+                        }
                     }
+                    a[w] = (int)word;
                 }
+                d[sj * RT * 64 + kh * 32] = a;
             }
-            a[w] = (int)word;
-        }
-        return a;
-    };
-    ks_v16i acc[2][4];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            acc[mt][q] = ks_v16i{};
-    ks_v4i bq[3][4];
-    auto step = [&](int s, int b) {
-        if (s + 2 < S)
-            loadb(s + 2, bq[(b + 2) % 3]);
-        const int jj = s / ksj, sj = s - jj * ksj;
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            const ks_v4i A = onehot(a_l[(32 * mt + r) * KSM_JMAX + jj], sj);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                acc[mt][q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-                    A, bq[b][q], acc[mt][q], 0, 0, 0);
         }
     };
-    loadb(0, bq[0]);
-    if (S > 1)
-        loadb(1, bq[1]);
-    int s = 0;
-    for (; s + 3 <= S; s += 3) {
-        step(s, 0);
-        step(s + 1, 1);
-        step(s + 2, 2);
-    }
-    if (s < S)
-        step(s, 0);
-    if (s + 1 < S)
-        step(s + 1, 1);
 
-    const int col = 32 * nt + r;
-    if (col > n)
-        return;
+    const int S = JC * ksj, SC = CJ * ksj;   // K-steps: all, of a chunk
+    const int nchunk = JC / CJ;
+    // (waves past the last tile repeat tile 0 and drop it)
+    const bool on = nt < nt_tiles;
+    const int8_t *bp = kski8 + ((size_t)(on ? nt : 0) * N + j0) * ksj * 4096 +
+                       q0 * 1024 + lane * 16;
+    auto loadb = [&](int s, ks_v4i (&b)[UW]) {
+        // (past the end the last step's blocks, unused)
+        const int8_t *p = bp + (size_t)min(s, S - 1) * 4096;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+        for (int q = 0; q < UW; ++q)
+            b[q] = *reinterpret_cast<const ks_v4i *>(p + q * 1024);
+    };
+    ks_v16i acc[RT][UW];
+#pragma unroll
+    for (int mt = 0; mt < RT; ++mt)
+#pragma unroll
+        for (int q = 0; q < UW; ++q)
+            acc[mt][q] = ks_v16i{};
+    constexpr int PF = RT == 4 ? 4 : 2;      // K-steps of key blocks in flight
+    ks_v4i bq[PF][UW];
+    build(0, load_u(0));
+    Pair u_nxt = load_u(1);
+#pragma unroll
+    for (int k = 0; k < PF; ++k)
+        loadb(k, bq[k]);
+    __syncthreads();
+    for (int c = 0; c < nchunk; ++c) {
+        build((c + 1) & 1, u_nxt);      // (after the last chunk: unused)
+        u_nxt = load_u(c + 2);
+        // A of the chunk's K-steps, read one ahead
+        const ks_v4i *as = al + (c & 1) * CJ * (ksj * RT * 64 + PADJ) + lane;
+        int sj = 0;
+        ks_v4i av[2][RT];
+        auto loada = [&](ks_v4i (&a)[RT]) {
+#pragma unroll
+            for (int mt = 0; mt < RT; ++mt)
+                a[mt] = as[mt * 64];
+            as += RT * 64;
+            if (++sj == ksj) {
+                sj = 0;
+                as += PADJ;
+            }
+        };
+        loada(av[0]);
+        // SC is a multiple of PF: CJ is
+        constexpr int UNROLL = KSJ > 0 ? CJ * KSJ / PF : 1;
+#pragma unroll(UNROLL)
+        for (int s = 0; s < (KSJ > 0 ? CJ * KSJ : SC); s += PF) {
+#pragma unroll
+            for (int k = 0; k < PF; ++k) {
+                // (past the chunk's end: the next buffer's words, unused)
+                loada(av[(k + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int mt = 0; mt < RT; ++mt)
+#pragma unroll
+                    for (int q = 0; q < UW; ++q)
+                        acc[mt][q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
+                            av[k & 1][mt], bq[k][q], acc[mt][q], 0, 0, 0);
+                loadb(c * SC + s + k + PF, bq[k]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __syncthreads();
+    }
+
+    // recombine the wave's limbs; with two waves per tile the second hands
+    // its sums over
+    uint32_t x[RT][16];
+#pragma unroll
+    for (int mt = 0; mt < RT; ++mt)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const int m = 32 * mt + 8 * (v >> 2) + 4 * kh + (v & 3);
-            uint32_t *dst = dst_l[m];
-            if (!dst)
-                continue;
-            const uint32_t x = (uint32_t)acc[mt][0][v] +
-                               ((uint32_t)acc[mt][1][v] << 8) +
-                               ((uint32_t)acc[mt][2][v] << 16) +
-                               ((uint32_t)acc[mt][3][v] << 24);
-            atomicSub(dst + col, x);
+            uint32_t y = 0;
+#pragma unroll
+            for (int q = 0; q < UW; ++q)
+                y += (uint32_t)acc[mt][q][v] << (8 * q);
+            x[mt][v] = y << (8 * q0);
         }
+    if constexpr (UW == 2) {
+        uint32_t *part = reinterpret_cast<uint32_t *>(ks_smem) +
+                         (wave >> 1) * RT * 16 * 64 + lane;
+        if (q0 != 0)
+#pragma unroll
+            for (int mt = 0; mt < RT; ++mt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    part[(mt * 16 + v) * 64] = x[mt][v];
+        __syncthreads();
+        if (q0 != 0)
+            return;
+#pragma unroll
+        for (int mt = 0; mt < RT; ++mt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                x[mt][v] += part[(mt * 16 + v) * 64];
+    }
+    const int col = 32 * nt + (lane & 31), kh = lane >> 5;
+    if (!on || col > n)
+        return;
+#pragma unroll
+    for (int mt = 0; mt < RT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            uint32_t *o = dst_l[32 * mt + 8 * (v >> 2) + 4 * kh + (v & 3)];
+            if (o)
+                atomicSub(o + col, x[mt][v]);
+        }
+}
+
+// Dynamic LDS of k_ks_mfma: two chunks of one-hot digits, or the hand-over
+// of limb sums.
+size_t ks_mfma_smem(int RT, int ksj)
+{
+    // (and the K-step read past the last chunk's end)
+    const size_t a = (size_t)2 * (KSM_THREADS * ksj * 32 + 16 * 16) +
+                     (size_t)RT * 64 * 16;
+    const size_t h = RT == 4 ? (size_t)4 * RT * 16 * 64 * 4 : 0;
+    return a > h ? a : h;
+}
+
+template <int RT, bool LEVEL>
+int ks_mfma_launch(const Ctx *c, const uint32_t *in, uint32_t *out, int B,
+                   KsLevel lv, hipStream_t s)
+{
+    const Shape &sh = c->sh;
+    constexpr int ROWS = 32 * RT;
+    const int nt_tiles = (sh.n + 1 + 31) / 32;
+    const int ng = (nt_tiles * 4 * RT + 63) / 64;
+    const int mg = (B + ROWS - 1) / ROWS;
+    // Split j into kc ranges.  The workgroups run in rounds of one per CU,
+    // and a workgroup costs about its j range plus 24 j (its start and its
+    // atomic fold; 4, 10 and 24 compared over widths: 24 takes 107 us at
+    // 1100 default ciphertexts where 10 takes 119, and 1-3% less at 1024
+    // large ones, the others are alike), so take the split with the least
+    // rounds x (j range + 24), the fewest ranges among equals; ranges are
+    // multiples of 16 j (whole chunks).
+    int jchunk = sh.N;
+    long best = -1;
+    for (int jc = sh.N; jc >= 16; jc -= 16) {
+        const int kk = (sh.N + jc - 1) / jc;
+        const long rounds = ((long)mg * ng * kk + c->cus - 1) / c->cus;
+        const long cost = rounds * (jc + 24);
+        if (best < 0 || cost < best) {
+            best = cost;
+            jchunk = jc;
+        }
+    }
+    const int kc = (sh.N + jchunk - 1) / jchunk;
+    auto fn = sh.gamma == 1    ? &k_ks_mfma<RT, LEVEL, -1>
+              : c->ks_ksj == 1 ? &k_ks_mfma<RT, LEVEL, 1>
+              : c->ks_ksj == 2 ? &k_ks_mfma<RT, LEVEL, 2>
+                               : &k_ks_mfma<RT, LEVEL, 0>;
+    hipLaunchKernelGGL(fn, dim3(mg, ng, kc), dim3(KSM_THREADS),
+                       ks_mfma_smem(RT, c->ks_ksj), s, c->ksk_i8, in, out, B,
+                       lv, sh.n, sh.N, sh.gamma, sh.t, c->ks_ksj, nt_tiles,
+                       jchunk);
+    CGGI_HIP_TRY(hipGetLastError());
+    return CGGI_OK;
 }
 
 template <bool LEVEL>
@@ -380,44 +514,15 @@ int ks_mfma_dispatch(const Ctx *c, const uint32_t *in, uint32_t *out, int B,
                      KsLevel lv, hipStream_t s)
 {
     const Shape &sh = c->sh;
-    const int nt_tiles = (sh.n + 1 + 31) / 32;
-    const int ng = (nt_tiles + KSM_WAVES - 1) / KSM_WAVES;
-    const int waves = (nt_tiles + ng - 1) / ng;
-    const int mg = (B + KSM_ITEMS - 1) / KSM_ITEMS;
-    // Split j into kc ranges (at most KSM_JMAX j each, at least 16).  The
-    // workgroups run in rounds of (CUs x resident workgroups per CU; one at
-    // 212 VGPRs), and a workgroup costs about its j range plus 10 j (the
-    // load of its a' and its atomic fold: fitted to launches of 4 to 64
-    // ranges of 1024 default ciphertexts on the MI355X), so take the split
-    // with the least rounds x (j range + 10), the fewest ranges among
-    // equals.  Filling the GPU twice over instead (528 workgroups, three
-    // rounds) was 25% slower at 1024 default ciphertexts.
-    const long slots = (long)c->cus * c->ks_wg_per_cu;
-    const int kc_lo = (sh.N + KSM_JMAX - 1) / KSM_JMAX;
-    const int kc_hi = std::max(kc_lo, std::max(1, sh.N / 16));
-    int jchunk = (sh.N + kc_lo - 1) / kc_lo;
-    long best = -1;
-    for (int k = kc_lo; k <= kc_hi; ++k) {
-        const int jc = (sh.N + k - 1) / k;
-        const int kk = (sh.N + jc - 1) / jc;
-        const long rounds = ((long)mg * ng * kk + slots - 1) / slots;
-        const long cost = rounds * (jc + 10);
-        if (best < 0 || cost < best) {
-            best = cost;
-            jchunk = jc;
-        }
-    }
-    const int kc = (sh.N + jchunk - 1) / jchunk;
     const size_t total = (size_t)B * (sh.n + 1);
     const int init_blocks = (int)std::min<size_t>((total + 255) / 256, 65536);
     hipLaunchKernelGGL(k_ks_init<LEVEL>, dim3(init_blocks), dim3(256), 0, s,
                        in, out, B, lv, sh.n, sh.N);
     CGGI_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_ks_mfma<LEVEL>, dim3(mg, ng, kc), dim3(64 * waves), 0,
-                       s, c->ksk_i8, in, out, B, lv, sh.n, sh.N, sh.gamma,
-                       sh.t, c->ks_ksj, nt_tiles, jchunk);
-    CGGI_HIP_TRY(hipGetLastError());
-    return CGGI_OK;
+    // four row tiles from two on: 64 default ciphertexts 25.5 us against 28.0
+    // with two; 37 take 24.0 against 23.3, 1 takes 22.3 against 17.5
+    return B > 48 ? ks_mfma_launch<4, LEVEL>(c, in, out, B, lv, s)
+                  : ks_mfma_launch<2, LEVEL>(c, in, out, B, lv, s);
 }
 
 template <bool LEVEL>
@@ -449,6 +554,20 @@ int ks_dispatch(const Ctx *c, const uint32_t *in, uint32_t *out, int B,
 
 } // namespace
 
+template <int KSJ> static int ks_mfma_attrs()
+{
+    const void *fn[4] = {
+        reinterpret_cast<const void *>(&k_ks_mfma<2, false, KSJ>),
+        reinterpret_cast<const void *>(&k_ks_mfma<2, true, KSJ>),
+        reinterpret_cast<const void *>(&k_ks_mfma<4, false, KSJ>),
+        reinterpret_cast<const void *>(&k_ks_mfma<4, true, KSJ>)};
+    for (const void *f : fn)
+        CGGI_HIP_TRY(hipFuncSetAttribute(
+            f, hipFuncAttributeMaxDynamicSharedMemorySize,
+            (int)ks_mfma_smem(4, 4)));
+    return CGGI_OK;
+}
+
 int keyswitch_make_key(Ctx *c, hipStream_t s)
 {
     const Shape &sh = c->sh;
@@ -463,21 +582,12 @@ int keyswitch_make_key(Ctx *c, hipStream_t s)
                                        "key failed");
     }
     c->ks_ksj = ksj;
-    // resident workgroups per CU of the GEMM at its launch shape (the
-    // split of j over workgroups is sized from it)
-    {
-        const int ng = (nt_tiles + KSM_WAVES - 1) / KSM_WAVES;
-        const int waves = (nt_tiles + ng - 1) / ng;
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &nb, reinterpret_cast<const void *>(&k_ks_mfma<true>),
-                64 * waves, 0) == hipSuccess) {
-            if (nb > 0)
-                c->ks_wg_per_cu = nb;
-        } else {
-            (void)hipGetLastError();   // keep one per CU; clear the error
-        }
-    }
+    int rc = sh.gamma == 1 ? ks_mfma_attrs<-1>()
+             : ksj == 1    ? ks_mfma_attrs<1>()
+             : ksj == 2    ? ks_mfma_attrs<2>()
+                           : ks_mfma_attrs<0>();
+    if (rc)
+        return rc;
     hipLaunchKernelGGL(k_ksk_to_i8, dim3(4096), dim3(256), 0, s, c->ksk,
                        reinterpret_cast<uint32_t *>(c->ksk_i8), sh.n, sh.N,
                        sh.t, sh.gamma, ksj, nt_tiles);
