@@ -33,15 +33,16 @@
 //
 // Work split.  One workgroup per bootstrap.  A step has four phases between
 // barriers: (0) every thread rotates, subtracts and takes the digits of its
-// coefficients; (1) a wave per digit polynomial runs a whole forward
-// transform, PPL = 8 points per lane (16 at N = 2048); (2) a thread per
-// point sums the 2l products for the four outputs (component, key half);
-// (3) a wave per output runs the inverse transform, rounds and adds into
-// the accumulator.  A wave's transform is three register passes with two
-// exchanges through its own row of LDS, which need no barrier; rows are
-// padded or swizzled so that every 16 lanes of a 16-byte access fall in
-// distinct banks (a conflict-free exchange of 8 KB takes 140 cycles, three
-// quarters of it the write; an unswizzled one 360).
+// coefficients; (1) a wave per digit polynomial (per two at N = 512 and 256;
+// two waves at N = 2048) runs a whole forward transform, PPL = 8 points per
+// lane (4 at N = 256); (2) a thread per point sums the 2l products for the
+// four outputs (component, key half); (3) a wave per output runs the inverse
+// transform, rounds and adds into the accumulator.  A wave's transform is
+// three register passes with two exchanges through its own row of LDS, which
+// need no barrier (N = 256: see quad_forward); rows are padded or swizzled so
+// that every 16 lanes of a 16-byte access fall in distinct banks (a
+// conflict-free exchange of 8 KB takes 140 cycles, three quarters of it the
+// write; an unswizzled one 360).
 //
 // What bounds it: at N = 1024 a step is a chain of about 9,000 cycles (LDS
 // writes and f64 issue of the six and four transform waves, the key's 192
@@ -73,7 +74,8 @@ template <int N> struct FCfg {
     static constexpr int H = N == 2048 ? 2 : 1;
     static constexpr int MS = M / H;
     static constexpr int LOGM = __builtin_ctz(MS);
-    static constexpr int RB = 3;
+    static constexpr bool QUAD = N == 256;       // (see quad_forward)
+    static constexpr int RB = QUAD ? 2 : 3;
     static constexpr int PPL = 1 << RB;          // points per lane
     static constexpr int LPF = MS / PPL;         // lanes per transform
     static constexpr int FPW = 64 / LPF;         // transforms per wave
@@ -84,8 +86,19 @@ template <int N> struct FCfg {
     static constexpr int THREADS = MS, WAVES = MS / 64;
     static constexpr int TW2 = NTW, TW3 = NTW + PPL * NTW; // table offsets
     static constexpr int TWX = TW3 + LPF * NTW;  // H = 2: [MS] values X
-    static constexpr bool PAD = LAST == 3;       // padded rows (see fslot)
-    static constexpr int ROW = PAD ? MS + MS / 8 : MS; // slots of an LDS row
+    static constexpr int TW4 = TW3 + 16 * NTW;   // QUAD: [LPF]
+    static constexpr bool PAD = !QUAD && LAST == 3; // padded rows (see fslot)
+    // slots of an LDS row
+    static constexpr int ROW = QUAD ? MS + 8 : PAD ? MS + MS / 8 : MS;
+    // a lane's transform among its wave's, and its place in it
+    static __device__ __forceinline__ int tf(int lane)
+    {
+        return QUAD ? lane >> 3 & 1 : lane / LPF;
+    }
+    static __device__ __forceinline__ int tlane(int lane)
+    {
+        return QUAD ? lane >> 4 << 3 | (lane & 7) : lane % LPF;
+    }
 };
 
 // Slot of index (a, b, c) in a transform's exchange row, such that every 16
@@ -199,6 +212,7 @@ __device__ __forceinline__ void reg_stages(d2 (&v)[PPL], const d2 *tw)
 // A lane's twiddles: pass 1 (the same for every lane), 2 and 3.
 template <int N> struct Tw {
     d2 w1[FCfg<N>::NTW], w2[FCfg<N>::NTW], w3[FCfg<N>::NTW];
+    d2 w4;                          // QUAD
     __device__ __forceinline__ void load(const double *__restrict__ t, int lf)
     {
         using C = FCfg<N>;
@@ -207,7 +221,11 @@ template <int N> struct Tw {
         for (int k = 0; k < C::NTW; ++k) {
             w1[k] = t2[k];
             w2[k] = t2[C::TW2 + (lf >> C::LAST) * C::NTW + k];
-            w3[k] = t2[C::TW3 + lf * C::NTW + k];
+            w3[k] = t2[C::TW3 + (C::QUAD ? lf & 15 : lf) * C::NTW + k];
+        }
+        if constexpr (C::QUAD) {
+            w4 = t2[C::TW4 + lf];
+            asm volatile("" : "+v"(w4.x), "+v"(w4.y));
         }
         // arrived before any loop: a use inside one would otherwise wait for
         // every load the loop has in flight
@@ -219,6 +237,105 @@ template <int N> struct Tw {
     }
 };
 
+// Swap the points' register bits 1 and 0 with lane bits 5 (W32) and 4 (W16).
+template <bool W32, bool W16>
+__device__ __forceinline__ void swap_lanes(d2 (&v)[4])
+{
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    u4 w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        w[k] = __builtin_bit_cast(u4, v[k]);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        if constexpr (W32)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const auto r = __builtin_amdgcn_permlane32_swap(
+                    w[k][d], w[k + 2][d], false, false);
+                w[k][d] = r[0];
+                w[k + 2][d] = r[1];
+            }
+        if constexpr (W16)
+#pragma unroll
+            for (int k = 0; k < 4; k += 2) {
+                const auto r = __builtin_amdgcn_permlane16_swap(
+                    w[k][d], w[k + 1][d], false, false);
+                w[k][d] = r[0];
+                w[k + 1][d] = r[1];
+            }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        v[k] = __builtin_bit_cast(d2, w[k]);
+}
+
+// The transforms of N = 256, 128 points on 32 lanes of four.  Index bits n6
+// .. n0 become result bits b0 .. b6, the top one first: registers n6 n5,
+// lane bits 5 4 2 1 0 n4 .. n0 (bit 3 is the transform); two stages, n4 n3
+// swapped into the registers, two stages, an exchange through LDS that
+// leaves n2 n1 in the registers, n0 on lane bit 5 and b0 .. b3 on bits 4 2 1
+// 0, two stages, n0 swapped in, one stage.  The 8-point lanes of the longer
+// transforms would leave one busy wave per phase, whose chain of f64
+// instructions (5 cycles each for a lone wave) and exchanges was most of a
+// step: 0.278 -> 0.213 ms for 128 steps of one bootstrap (l = 2), 2.79 ->
+// 2.35 ms for 8192.  Slot of (b0 .. b3, n2 n1 n0) in
+// the exchange row: 8 consecutive lanes fall in distinct banks of one half
+// for either side, and the wave's other row (an odd multiple of 8 slots
+// away) in the other half.
+__device__ __forceinline__ int qslot(int b, int n)
+{
+    return b << 3 | (n ^ (b & 7));
+}
+
+template <class F>
+__device__ __forceinline__ void quad_forward(d2 (&v)[4], d2 *row, int lf,
+                                             const Tw<256> &tw, F mid)
+{
+    reg_stages<4, 2, false>(v, tw.w1);
+    swap_lanes<true, true>(v);
+    mid(0);
+    reg_stages<4, 2, false>(v, tw.w2);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        row[qslot(lf >> 3 << 2 | k, lf & 7)] = v[k];
+    mid(1);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        v[k] = row[qslot(lf & 15, k << 1 | lf >> 4)];
+    reg_stages<4, 2, false>(v, tw.w3);
+    swap_lanes<true, false>(v);
+    bf_fwd<false>(v[0], v[2], tw.w4);
+    bf_fwd<true>(v[1], v[3], tw.w4);
+    wave_sync();
+}
+
+template <class F>
+__device__ __forceinline__ void quad_inverse(d2 (&v)[4], d2 *row, int lf,
+                                             const Tw<256> &tw, F mid)
+{
+    bf_inv<false>(v[0], v[2], tw.w4);
+    bf_inv<true>(v[1], v[3], tw.w4);
+    swap_lanes<true, false>(v);
+    reg_stages<4, 2, true>(v, tw.w3);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        row[qslot(lf & 15, k << 1 | lf >> 4)] = v[k];
+    mid(0);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        v[k] = row[qslot(lf >> 3 << 2 | k, lf & 7)];
+    reg_stages<4, 2, true>(v, tw.w2);
+    mid(1);
+    swap_lanes<true, true>(v);
+    reg_stages<4, 2, true>(v, tw.w1);
+    wave_sync();
+}
+
 // Forward transform of the lane's points v (register index a, lane (b, c)),
 // through the transform's own LDS row; on return the registers are pass 3's
 // (b's low bits, c) on lane (a, b's high bits).
@@ -228,6 +345,10 @@ __device__ __forceinline__ void fft_forward(d2 (&v)[FCfg<N>::PPL], d2 *row,
                                             int lf, const Tw<N> &tw, F mid)
 {
     using C = FCfg<N>;
+    if constexpr (C::QUAD) {
+        quad_forward(v, row, lf, tw, mid);
+        return;
+    } else {
     constexpr int CM = (1 << C::LAST) - 1, LM = (1 << C::BS) - 1;
     reg_stages<C::PPL, C::RB, false>(v, tw.w1);
     wave_sync();
@@ -253,6 +374,7 @@ __device__ __forceinline__ void fft_forward(d2 (&v)[FCfg<N>::PPL], d2 *row,
                             k & CM)];
     reg_stages<C::PPL, C::LAST, false>(v, tw.w3);
     wave_sync();
+    }
 }
 
 // The inverse (unscaled) of fft_forward.
@@ -261,6 +383,10 @@ __device__ __forceinline__ void fft_inverse(d2 (&v)[FCfg<N>::PPL], d2 *row,
                                             int lf, const Tw<N> &tw, F mid)
 {
     using C = FCfg<N>;
+    if constexpr (C::QUAD) {
+        quad_inverse(v, row, lf, tw, mid);
+        return;
+    } else {
     constexpr int CM = (1 << C::LAST) - 1, LM = (1 << C::BS) - 1;
     reg_stages<C::PPL, C::LAST, true>(v, tw.w3);
     wave_sync();
@@ -286,6 +412,7 @@ __device__ __forceinline__ void fft_inverse(d2 (&v)[FCfg<N>::PPL], d2 *row,
         v[k] = row[fslot<N>(k, lf >> C::LAST, lf & CM)];
     reg_stages<C::PPL, C::RB, true>(v, tw.w1);
     wave_sync();
+    }
 }
 
 // bsk [n][2l][2][N] -> transforms [n][2l][4][M] of the key halves times 1/M
@@ -301,7 +428,7 @@ __global__ __launch_bounds__(64) void k_fft_key(
     using C = FCfg<N>;
     constexpr int H = C::H;
     __shared__ __align__(16) double rows[C::FPW * C::ROW * 2];
-    const int lane = threadIdx.x, lf = lane % C::LPF, f = lane / C::LPF;
+    const int lane = threadIdx.x, lf = C::tlane(lane), f = C::tf(lane);
     Tw<N> tw;
     tw.load(tab, lf);
     // polynomial index (i * 2l + r) * 4 + o
@@ -417,7 +544,7 @@ void k_bootstrap_fft(
         return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lf = lane % LPF, f = lane / LPF;
+    const int lf = C::tlane(lane), f = C::tf(lane);
     // (a last workgroup with fewer than NB bootstraps repeats its last one)
     const uint32_t *ct[NB];
 #pragma unroll
@@ -780,6 +907,13 @@ template <int N> std::vector<double> fft_table()
     push_twiddles(t, 0, 0, C::RB);
     for (int a = 0; a < C::PPL; ++a)
         push_twiddles(t, rev_bits(a, C::RB), C::RB, C::RB);
+    if constexpr (C::QUAD) {
+        for (int b = 0; b < 16; ++b)
+            push_twiddles(t, rev_bits(b, 4), 4, 2);
+        for (int f = 0; f < C::LPF; ++f)   // b0 .. b4, b5 = 0
+            push_twiddles(t, rev_bits((f & 15) << 2 | f >> 4 << 1, 6), 6, 1);
+        return t;
+    }
     for (int f = 0; f < C::LPF; ++f)
         for (int bl = 0; bl < (1 << C::BS); ++bl) {
             // prefix (a, b), b = (lane's low bits, bl)
