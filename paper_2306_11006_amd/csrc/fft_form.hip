@@ -912,14 +912,14 @@ template <int N> std::vector<double> fft_table()
             push_twiddles(t, rev_bits(b, 4), 4, 2);
         for (int f = 0; f < C::LPF; ++f)   // b0 .. b4, b5 = 0
             push_twiddles(t, rev_bits((f & 15) << 2 | f >> 4 << 1, 6), 6, 1);
-        return t;
+    } else {
+        for (int f = 0; f < C::LPF; ++f)
+            for (int bl = 0; bl < (1 << C::BS); ++bl) {
+                // prefix (a, b), b = (lane's low bits, bl)
+                const unsigned pre = ((unsigned)f << C::BS) | (unsigned)bl;
+                push_twiddles(t, rev_bits(pre, 2 * C::RB), 2 * C::RB, C::LAST);
+            }
     }
-    for (int f = 0; f < C::LPF; ++f)
-        for (int bl = 0; bl < (1 << C::BS); ++bl) {
-            // prefix (a, b), b = (lane's low bits, bl)
-            const unsigned pre = ((unsigned)f << C::BS) | (unsigned)bl;
-            push_twiddles(t, rev_bits(pre, 2 * C::RB), 2 * C::RB, C::LAST);
-        }
     if (C::H == 2)
         for (int j = 0; j < C::MS; ++j) {
             // the root of register j / LPF of lane j mod LPF
