@@ -119,7 +119,6 @@ static void free_ctx(Ctx *c)
     (void)hipFree(c->tw_fwd);
     (void)hipFree(c->tw_inv);
     (void)hipFree(c->bsk_fft);
-    (void)hipFree(c->fft_tw);
     (void)hipFree(c->bsk_i8);
     (void)hipFree(c->corr_i8);
     (void)hipFree(c->bsk_k8);
@@ -324,6 +323,31 @@ int cggi_params_check(const cggi_params_t *params)
     return shape_of(params, nullptr);
 }
 
+// The device's data and the keys of a new context.
+static int make_keys(Ctx *c, const uint32_t *bsk, bool fft, hipStream_t s)
+{
+    int rc;
+    if (hipGetDevice(&c->device) != hipSuccess ||
+        hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount,
+                              c->device) != hipSuccess || c->cus < 1)
+        return set_error(CGGI_E_HIP, "hipGetDevice / CU count failed");
+    if ((rc = scratch_address(c->device, &c->scratch)) ||
+        (fft && (rc = fft_make_key(c, bsk, s))))
+        return rc;
+    // with the FFT kernel the NTT form's own kernel is never launched
+    if ((c->forms & CGGI_FORM_NTT) && !c->bsk_fft &&
+        ((rc = ntt_make_tables(c, s)) || (rc = ntt_transform_bsk(c, bsk, s))))
+        return rc;
+    if ((c->forms & CGGI_FORM_INT8) && (rc = int8_make_key(c, bsk, s)))
+        return rc;
+    if ((rc = keyswitch_make_key(c, s)))
+        return rc;
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess)
+        return hip_error(e, "hipStreamSynchronize after key derivation");
+    return CGGI_OK;
+}
+
 int cggi_ctx_create(const cggi_params_t *params, const uint32_t *d_bsk,
                     const uint32_t *d_ksk, uint32_t forms, void *stream,
                     cggi_ctx **out)
@@ -344,49 +368,26 @@ int cggi_ctx_create(const cggi_params_t *params, const uint32_t *d_bsk,
         return set_error(CGGI_E_SHAPE, "bsk and ksk must be non-NULL and "
                                        "4-byte aligned");
     hipStream_t s = (hipStream_t)stream;
-    cggi_ctx *c = new cggi_ctx();
-    c->p = *params;
-    c->sh = sh;
-    c->forms = forms;
-    c->ksk = d_ksk;
-    if (hipGetDevice(&c->device) != hipSuccess ||
-        hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount,
-                              c->device) != hipSuccess || c->cus < 1) {
-        free_ctx(c);
-        return set_error(CGGI_E_HIP, "hipGetDevice / CU count failed");
-    }
-    if ((rc = scratch_address(c->device, &c->scratch))) {
-        free_ctx(c);
-        return rc;
-    }
-    if ((rc = fft_make_key(c, d_bsk, s))) {
-        free_ctx(c);
-        return rc;
-    }
-    // with the FFT kernel the NTT form's own kernel is never launched
-    if ((forms & CGGI_FORM_NTT) && !c->bsk_fft) {
-        if ((rc = ntt_make_tables(c, s)) || (rc = ntt_transform_bsk(c, d_bsk, s))) {
-            free_ctx(c);
-            return rc;
+    // where the other keys don't fit beside the FFT kernel's, without it
+    for (int fft = 1; fft >= 0; --fft) {
+        cggi_ctx *c = new cggi_ctx();
+        c->p = *params;
+        c->sh = sh;
+        c->forms = forms;
+        c->ksk = d_ksk;
+        rc = make_keys(c, d_bsk, fft, s);
+        if (!rc) {
+            *out = c;
+            return CGGI_OK;
         }
-    }
-    if (forms & CGGI_FORM_INT8) {
-        if ((rc = int8_make_key(c, d_bsk, s))) {
-            free_ctx(c);
-            return rc;
-        }
-    }
-    if ((rc = keyswitch_make_key(c, s))) {
+        const bool again = c->bsk_fft && rc == CGGI_E_NOMEM;
+        (void)hipStreamSynchronize(s);
         free_ctx(c);
-        return rc;
+        if (!again)
+            break;
+        (void)hipGetLastError();
     }
-    hipError_t e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-        free_ctx(c);
-        return hip_error(e, "hipStreamSynchronize after key derivation");
-    }
-    *out = c;
-    return CGGI_OK;
+    return rc;
 }
 
 int cggi_ctx_destroy(cggi_ctx *ctx)

@@ -44,12 +44,16 @@
 // conflict-free exchange of 8 KB takes 140 cycles, three quarters of it the
 // write; an unswizzled one 360).
 //
-// What bounds it: at N = 1024 a step is a chain of about 9,000 cycles (LDS
-// writes and f64 issue of the six and four transform waves, the key's 192
-// KB through one CU's vector cache at 64 bytes a cycle hidden behind them),
-// 2.4 ms for up to 256 bootstraps against 2.8 to 8.5 ms for the int8
-// kernels and 10.3 ms for the modular transform; wider batches run at the
-// chip's power limit (the clock falls from 2.4 to 2.0 GHz).
+// What bounds it: at N = 1024 a step takes 8,400 cycles for one bootstrap and
+// 15,300 for two.  The VALU issues 3,900 wave instructions of it per bootstrap
+// (3,200 are the transforms' and sums' f64 work, 4.4 to 5.1 cycles each on a
+// SIMD), the LDS is active 3,460 cycles, and the key's 192 KB come through the
+// CU's vector cache at 64 bytes a cycle behind them; since the waves leave a
+// barrier together and run the same phase, VALU and LDS time mostly add up.
+// Default set (n = 630, l = 3): 2.2 ms for one bootstrap and 2.7 for 256,
+// against 2.8 to 8.5 ms for the int8 kernels and 10.3 for the modular
+// transform; 8.0 ms for 1024, against 17.9 and 31.6.  Large set (n = 742,
+// N = 2048, l = 2): 4.0 ms for one, 32.5 ms for 2000.
 #include "internal.hpp"
 
 #include <cmath>
@@ -963,19 +967,19 @@ template <int N> int fft_key_t(Ctx *c, const uint32_t *bsk, hipStream_t s)
 {
     using C = FCfg<N>;
     const Shape &sh = c->sh;
-    const std::vector<double> t = fft_table<N>();
+    c->fft_tab = fft_table<N>();
     const int npoly = sh.n * 2 * sh.l * 4;
-    if (hipMalloc(&c->fft_tw, t.size() * sizeof(double)) != hipSuccess ||
-        hipMalloc(&c->bsk_fft, (size_t)npoly * C::M * 16) != hipSuccess) {
+    const size_t words = (size_t)npoly * C::M * 2;
+    const size_t tab = c->fft_tab.size() * sizeof(double);
+    if (hipMalloc(&c->bsk_fft, words * sizeof(double) + tab) != hipSuccess) {
         // the context then serves its forms with their own kernels
         (void)hipGetLastError();
-        (void)hipFree(c->fft_tw);
-        c->fft_tw = c->bsk_fft = nullptr;
+        c->bsk_fft = nullptr;
         return CGGI_OK;
     }
-    CGGI_HIP_TRY(hipMemcpyAsync(c->fft_tw, t.data(), t.size() * sizeof(double),
+    c->fft_tw = c->bsk_fft + words;
+    CGGI_HIP_TRY(hipMemcpyAsync(c->fft_tw, c->fft_tab.data(), tab,
                                 hipMemcpyHostToDevice, s));
-    CGGI_HIP_TRY(hipStreamSynchronize(s));   // t leaves scope
     hipLaunchKernelGGL(k_fft_key<N>, dim3((npoly + C::FPW - 1) / C::FPW),
                        dim3(64), 0, s, bsk, c->fft_tw, c->bsk_fft, npoly);
     CGGI_HIP_TRY(hipGetLastError());

@@ -39,7 +39,8 @@ struct cggi_ctx {
     // FFT kernel (fft_form.hip), serving both forms; null where its error
     // bound does not prove the rounding
     double *bsk_fft = nullptr;    // [n][2l][4][N/2] complex, key halves
-    double *fft_tw = nullptr;     // its twiddle table
+    double *fft_tw = nullptr;     // its twiddle table, in the same allocation
+    std::vector<double> fft_tab;  // the table's host copy (its upload's source)
     // INT8 form
     int8_t *bsk_i8 = nullptr;     // [n][R][2][4][elen] limb windows
     uint32_t *corr_i8 = nullptr;  // [n][2][N] digit-offset correction (N <= 1024)

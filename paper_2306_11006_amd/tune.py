@@ -11,8 +11,9 @@ HIP events around the launch), keeps the fastest per width, and compresses
 the winners into a plan of (kind, cap) entries: entry k takes the batches
 of cap[k-1] + 1 .. cap[k] bootstraps, so a width between two grid points
 goes to the kernel that won the larger one.  It also times the NTT form per
-width, so a caller can pick the faster form per level (best_form; at
-N = 2048 the NTT form wins).
+width, so a caller can pick the faster form per level (best_form; the NTT
+form wins wherever the double-precision transform serves it, while an
+installed plan keeps the int8 form on the kernels above).
 
 Tables are cached as JSON keyed by parameter set, device, CU count and the
 library build (cache directory: $CGGI_TUNE_CACHE, else ~/.cache/cggi_tune).
