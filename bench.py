@@ -66,7 +66,7 @@ def code_sha256(path):
 
 def stored_traffic(profile="profiles/eval_level_1024_nand_default.md",
                    kernel=None):
-    """HBM bytes per launch of the int8 bootstrap kernel from the committed
+    """HBM bytes per launch of the bootstrap kernel from the committed
     FETCH_SIZE / WRITE_SIZE counter runs (each scaled by the factor the same
     counter showed for a copy of known size), or None when the counters were
     taken on another version of the kernel source or (when `kernel` is
@@ -478,7 +478,10 @@ def main():
         log(f"[bench] int8 GEMM kernels: {gemm['ms_per_step']:.3f} ms/step")
     if fft:
         roof = fft_roof(r, G)
-        roof["traffic"] = None
+        roof.update({
+            "traffic": (stored_traffic(kernel=roof["kernel"]) if G == 1024
+                        else None),
+            "traffic_unit": "HBM bytes per launch (rocprofv3 counters)"})
     elif main_form == "int8":
         roof = int8_roof(r, G)
         roof.update({
