@@ -1001,12 +1001,13 @@ int fft_launch_l(const Ctx *c, const uint32_t *in, const uint32_t *testv,
         // Batches wider than the chip: two bootstraps per workgroup in
         // rounds of twice the CUs, one per workgroup for a rest of at most
         // half a round (and for every narrower batch: a step of two takes
-        // 1.4 times a step of one).  A count read on the device is split
+        // 1.8 times a step of one).  A count read on the device is split
         // there, so both are launched; the one with no share exits at once.
         pair_width = 2 * c->cus;
         grid = B < c->cus ? B : c->cus;
         const int rest = B % pair_width;
-        const bool pairs = B > c->cus, ones = d_count || (rest && rest <= c->cus);
+        const bool pairs = B > c->cus;
+        const bool ones = d_count || (rest && rest <= c->cus);
         if (pairs) {
             hipLaunchKernelGGL((k_bootstrap_fft<N, 2, L, KR, FWPE>),
                                dim3((B + 1) / 2), dim3(FCfg<N>::THREADS),

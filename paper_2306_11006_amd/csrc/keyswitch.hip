@@ -21,7 +21,7 @@
 // GEMM on v_mfma_i32_32x32x32_i8 (k_ks_mfma): with the one-hot digit matrix
 // A[g][(j, p, h)] = (d_{g,j,p} == h) and the key as four signed int8 limbs,
 // sum_{j,p} ksk[j][p][d_{g,j,p}][c] = sum_k A[g][k] * ksk[k][c].  The key
-// (tens of MB) is then streamed once per 64 ciphertexts instead of being
+// (tens of MB) is then streamed once per 128 ciphertexts instead of being
 // gathered row by row for every ciphertext.
 #include "internal.hpp"
 
