@@ -44,9 +44,9 @@
 // conflict-free exchange of 8 KB takes 140 cycles, three quarters of it the
 // write; an unswizzled one 360).
 //
-// What bounds it: at N = 1024 a step takes 8,400 cycles for one bootstrap and
-// 15,300 for two.  The VALU issues 3,900 wave instructions of it per bootstrap
-// (3,200 are the transforms' and sums' f64 work, 4.4 to 5.1 cycles each on a
+// What bounds it: at N = 1024 a step takes 8,300 cycles for one bootstrap and
+// 15,300 for two.  The VALU issues 3,800 wave instructions of it per bootstrap
+// (3,100 are the transforms' and sums' f64 work, 4.4 to 5.1 cycles each on a
 // SIMD), the LDS is active 3,460 cycles, and the key's 192 KB come through the
 // CU's vector cache at 64 bytes a cycle behind them; since the waves leave a
 // barrier together and run the same phase, VALU and LDS time mostly add up.
@@ -213,6 +213,57 @@ __device__ __forceinline__ void reg_stages(d2 (&v)[PPL], const d2 *tw)
         }
 }
 
+// The inverse's last pass: the stages of the root (X^(2^NS) = i after the
+// deeper ones), whose twiddles are the same in every lane.  A difference is
+// turned by 1 - i tan instead of cos - i sin, two operations a butterfly less
+// (six), and the cosines are left to the caller's next multiplication
+// (root_scale); two halves that meet carry the same one or, at the last
+// stage's odd positions, a ratio of cosines for the multiply-add to take in.
+// A stage's error is at most 3u of its outputs' 2-norm, u each from the
+// difference, the tangent or ratio and the result, and the few u of
+// root_scale fit in what the bound above grants beyond that.
+template <int NS> __device__ __forceinline__ void root_stages(d2 (&v)[1 << NS])
+{
+    constexpr double TAN16 = 0.19891236737965800691;    // tan(pi/16)
+    constexpr double TAN516 = 1.4966057626654890177;    // tan(5 pi/16)
+    constexpr double TAN8 = 0.41421356237309504882;     // tan(pi/8)
+    constexpr double RATIO = 0.56645449735052153656;  // cos(5 pi/16)/cos(pi/16)
+    auto turn = [](d2 &x, d2 &y, double t, bool rot) {
+        const d2 d = {x.x - y.x, x.y - y.y};
+        x += y;
+        const d2 r = {fma(t, d.y, d.x), fma(-t, d.x, d.y)};
+        y = rot ? d2{r.y, -r.x} : r;
+    };
+    if constexpr (NS == 3)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            turn(v[2 * g], v[2 * g + 1], g >> 1 ? TAN516 : TAN16, g & 1);
+    constexpr int Q = 1 << (NS - 2);
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int k = 0; k < Q; ++k)
+            turn(v[2 * Q * g + k], v[2 * Q * g + Q + k], TAN8, g);
+#pragma unroll
+    for (int k = 0; k < 2 * Q; ++k) {
+        d2 &x = v[k], &y = v[k + 2 * Q];
+        const double rho = NS == 3 && (k & 1) ? RATIO : 1.0;
+        const d2 d = {fma(-rho, y.x, x.x), fma(-rho, y.y, x.y)};
+        x = {fma(rho, y.x, x.x), fma(rho, y.y, x.y)};
+        y = {d.x + d.y, d.y - d.x};
+    }
+}
+
+// The factor root_stages leaves out of register k.
+template <int NS> constexpr double root_scale(int k)
+{
+    constexpr double COS16 = 0.98078528040323044913;    // cos(pi/16)
+    constexpr double COS8 = 0.92387953251128675613;     // cos(pi/8)
+    constexpr double COS4 = 0.70710678118654752440;     // cos(pi/4)
+    return (NS == 3 && (k & 1) ? COS16 : 1.0) *
+           (k >> (NS - 2) & 1 ? COS8 : 1.0) * (k >> (NS - 1) & 1 ? COS4 : 1.0);
+}
+
 // A lane's twiddles: pass 1 (the same for every lane), 2 and 3.
 template <int N> struct Tw {
     d2 w1[FCfg<N>::NTW], w2[FCfg<N>::NTW], w3[FCfg<N>::NTW];
@@ -336,7 +387,7 @@ __device__ __forceinline__ void quad_inverse(d2 (&v)[4], d2 *row, int lf,
     reg_stages<4, 2, true>(v, tw.w2);
     mid(1);
     swap_lanes<true, true>(v);
-    reg_stages<4, 2, true>(v, tw.w1);
+    root_stages<2>(v);
     wave_sync();
 }
 
@@ -381,8 +432,8 @@ __device__ __forceinline__ void fft_forward(d2 (&v)[FCfg<N>::PPL], d2 *row,
     }
 }
 
-// The inverse (unscaled) of fft_forward.
-template <int N, class F>
+// The inverse of fft_forward, unscaled; ROOT: but for root_scale.
+template <int N, bool ROOT, class F>
 __device__ __forceinline__ void fft_inverse(d2 (&v)[FCfg<N>::PPL], d2 *row,
                                             int lf, const Tw<N> &tw, F mid)
 {
@@ -414,7 +465,10 @@ __device__ __forceinline__ void fft_inverse(d2 (&v)[FCfg<N>::PPL], d2 *row,
 #pragma unroll
     for (int k = 0; k < C::PPL; ++k)
         v[k] = row[fslot<N>(k, lf >> C::LAST, lf & CM)];
-    reg_stages<C::PPL, C::RB, true>(v, tw.w1);
+    if constexpr (ROOT)
+        root_stages<C::RB>(v);
+    else
+        reg_stages<C::PPL, C::RB, true>(v, tw.w1);
     wave_sync();
     }
 }
@@ -527,6 +581,12 @@ void k_bootstrap_fft(
     constexpr int ROW = C::ROW, H = C::H, MS = C::MS;
     constexpr int T = C::THREADS;
     constexpr int LOG2_2N = __builtin_ctz(2 * N);
+    // The inverse's last pass by root_stages where its chain of instructions
+    // is what a step waits for: one bootstrap of the default set 2.22 -> 2.17
+    // ms, 256 of them 2.67 -> 2.62, 512 toy ones 0.293 -> 0.286.  With two
+    // transforms per SIMD in the inverse phase it gains nothing (4096: 31.8 ->
+    // 32.1 ms) or loses (one bootstrap at N = 2048: 3.94 -> 4.11 ms).
+    constexpr bool ROOT = H == 1 && NB == 1;
     const int l = L ? L : l_rt;
     const int R = 2 * l;
     const int RB = (R > 4 ? R : 4) * H;          // rows of a bootstrap
@@ -817,7 +877,7 @@ void k_bootstrap_fft(
 #pragma unroll
             for (int k = 0; k < PPL; ++k)
                 v[k] = row[k * LPF + lf];
-            fft_inverse<N>(v, row, lf, tw, [&](int m) {
+            fft_inverse<N, ROOT>(v, row, lf, tw, [&](int m) {
                 if constexpr (ROLE == 4)
                     key_issue(min(i_nxt, n - 1), 0, kb[0], m * KL / 4,
                               (m + 1) * KL / 4);
@@ -828,10 +888,11 @@ void k_bootstrap_fft(
 #pragma unroll
             for (int k = 0; k < PPL; ++k) {
                 const double magic = 6755399441055744.0;
+                const double sc = ROOT ? root_scale<C::RB>(k) : 1.0;
                 const uint32_t re =
-                    (uint32_t)__double_as_longlong(v[k].x + magic) << hs;
+                    (uint32_t)__double_as_longlong(fma(v[k].x, sc, magic)) << hs;
                 const uint32_t im =
-                    (uint32_t)__double_as_longlong(v[k].y + magic) << hs;
+                    (uint32_t)__double_as_longlong(fma(v[k].y, sc, magic)) << hs;
                 __hip_atomic_fetch_add(ao + k * LPF, re, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
                 __hip_atomic_fetch_add(ao + k * LPF + MS, im, __ATOMIC_RELAXED,
