@@ -283,7 +283,10 @@ int cggi_ctx_check(cggi_ctx *ctx);
  * any other), as a time-out would: latency-mode kernels still running
  * stop at their next poll, later ones do nothing (their outputs are left
  * untouched) until cggi_ctx_check, which then returns CGGI_E_TIMEOUT and
- * clears the state.  Other INT8 kernels and the NTT form are unaffected.
+ * clears the state.  INT8 batches of latency mode's widths that run on the
+ * double-precision kernel keep that rule: while latency mode is on, each of
+ * their bootstraps is written as a whole or, once the word is set, not at
+ * all.  Wider INT8 batches and the NTT form are unaffected.
  * CGGI_OK also when the context has no latency mode. */
 int cggi_ctx_latency_abort(cggi_ctx *ctx);
 

@@ -603,9 +603,19 @@ void k_bootstrap_fft(
     if (g0 >= to)
         return;
     // narrow INT8 batches are refused while the latency-mode error word is
-    // set (cggi_ctx_latency_abort)
-    if (stop && count <= stop_cap && *stop)
-        return;
+    // set.  cggi_ctx_latency_abort sets it from another stream while launches
+    // run, so one thread reads it for the workgroup: a bootstrap is written
+    // as a whole or not at all.  (The word's place in the rows is first
+    // written after the step loop's first barrier.)
+    if (stop && count <= stop_cap) {
+        uint32_t *word = reinterpret_cast<uint32_t *>(smem);
+        if (threadIdx.x == 0)
+            *word = __hip_atomic_load(stop, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (*word)
+            return;
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lf = C::tlane(lane), f = C::tf(lane);
