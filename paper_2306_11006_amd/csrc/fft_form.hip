@@ -564,7 +564,10 @@ __device__ __forceinline__ void fft_share(int NB, int count, int pair_width,
 // levels) is a compile-time constant for the sets in use, 0 reads it at run
 // time.  A thread reads the key values of its slot (H points) KR digit rows
 // at a time, a batch ahead of their use (the first batch before the
-// barrier); KR = 2L holds the whole column, read during the transforms.
+// barrier); KR = 2L holds the whole column, read during the transforms.  (L =
+// 0 that read each row where it is used waited for every one: 200 steps of
+// 1024 bootstraps at N = 512, l = 4 took 4.12 ms, 2.02 a row ahead; the int8
+// kernels 2.98.)
 // WPE: waves per SIMD the registers are budgeted for.
 template <int N, int NB, int L, int KR, int WPE>
 __global__ __launch_bounds__(FCfg<N>::THREADS)
@@ -662,8 +665,8 @@ void k_bootstrap_fft(
     }
     // key values in flight: batch bt covers rows KR bt .. of the slot
     constexpr bool AHEAD = L > 0 && KR == 2 * L;
-    constexpr int NBT = L ? 2 * L / (KR ? KR : 1) : 1;
-    constexpr int KB = L ? (AHEAD ? 1 : 2) : 1, KL = L ? KR * 4 * H : 1;
+    constexpr int NBT = L ? 2 * L / KR : 1;
+    constexpr int KB = AHEAD ? 1 : 2, KL = KR * 4 * H;
     d2 kb[KB][KL];
     const d2 *key2 = reinterpret_cast<const d2 *>(key);
     auto key_issue = [&](int i, int bt, d2 (&dst)[KL], int q0, int q1) {
@@ -808,7 +811,7 @@ void k_bootstrap_fft(
             for (int t0 = fw * FPW; t0 >= 0 && t0 < nf; t0 += C::WAVES * FPW)
                 forward(t0, [](int) {});
         }
-        if constexpr (L && !AHEAD)
+        if constexpr (!AHEAD)
             key_issue(i, 0, kb[0], 0, KL);
         fft_barrier();
         // (2) the four outputs' sums over the digit polynomials, in place
@@ -846,8 +849,8 @@ void k_bootstrap_fft(
                     }
             }
         } else {
-            const d2 *kp = key2 + (size_t)i * R * 4 * M + tid;
-            for (int r = 0; r < R; ++r)
+            // R is even
+            auto sum_row = [&](int r, const d2 (&k)[KL]) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
                     d2 x[H];
@@ -856,9 +859,19 @@ void k_bootstrap_fft(
                     for (int o = 0; o < 4; ++o)
 #pragma unroll
                         for (int q = 0; q < H; ++q)
-                            mac(s[b][o][q], x[q],
-                                kp[((r * 4 + o) * H + q) * MS]);
+                            mac(s[b][o][q], x[q], k[o * H + q]);
                 }
+            };
+            int r = 0;
+            for (; r + 2 < R; r += 2) {
+                key_issue(i, r + 1, kb[1], 0, KL);
+                sum_row(r, kb[0]);
+                key_issue(i, r + 2, kb[0], 0, KL);
+                sum_row(r + 1, kb[1]);
+            }
+            key_issue(i, r + 1, kb[1], 0, KL);
+            sum_row(r, kb[0]);
+            sum_row(r + 1, kb[1]);
         }
 #pragma unroll
         for (int b = 0; b < NB; ++b)
@@ -1026,7 +1039,7 @@ template <int N, int NB, int L, int KR> int fft_attr1()
 
 template <int N, int L> int fft_attr()
 {
-    constexpr int KR = L ? FKR<N>(L) : 0;
+    constexpr int KR = L ? FKR<N>(L) : 1;
     int rc = fft_attr1<N, 1, L, KR>();
     if constexpr (FPAIR<N>(L))
         if (!rc)
@@ -1065,7 +1078,7 @@ int fft_launch_l(const Ctx *c, const uint32_t *in, const uint32_t *testv,
                  const uint32_t *stop, int stop_cap, hipStream_t s)
 {
     const Shape &sh = c->sh;
-    constexpr int KR = L ? FKR<N>(L) : 0;
+    constexpr int KR = L ? FKR<N>(L) : 1;
     const size_t smem = fft_smem(N, sh.l);
     int pair_width = 0, grid = B;
     if constexpr (FPAIR<N>(L)) {
