@@ -51,11 +51,11 @@ typedef struct {
 /* Forms of the negacyclic products inside the blind rotation.  Both give
  * bit-identical results.  Where a double-precision transform is proven to
  * round to the exact integers (csrc/fft_form.hip; Bg up to 2^13 or so, every
- * parameter set of params.py), both forms run on that kernel, which is
- * faster at every batch width; a context then keeps the key's transforms
- * (64 * n*2l*N bytes) instead of the NTT form's.  The kernels below serve the
- * other parameter sets and, for INT8, an explicit kernel plan
- * (cggi_ctx_int8_plan).
+ * parameter set of params.py), both forms run on that kernel; a context then
+ * keeps the key's transforms (64 * n*2l*N bytes) instead of the NTT form's.
+ * The kernels below serve the other parameter sets and, for INT8, an explicit
+ * kernel plan (cggi_ctx_int8_plan) and the widths where they are faster (wide
+ * batches at N <= 512 and Bg <= 2^7; cggi_ctx_transform tells).
  *  NTT : exact NTT modulo Q = 2^64 - 2^32 + 1 with the paper's generator
  *        (Section 5.4), centred lift, low 32 bits.
  *  INT8: exact split-limb block-Toeplitz GEMM on int8 MFMA with int32
@@ -331,6 +331,12 @@ int cggi_ctx_int8_plan(cggi_ctx *ctx, const int32_t *kinds,
 int cggi_ctx_int8_plan_get(const cggi_ctx *ctx, int32_t *kinds,
                            int32_t *caps, int32_t max, int32_t *count);
 int cggi_ctx_int8_limits(const cggi_ctx *ctx, int32_t *limits /* [7] */);
+
+/* The widest batch of `form` that a call made now runs on the
+ * double-precision kernel (see cggi_form_t): 0 for none, INT32_MAX for every
+ * batch.  Host state only.  CGGI_E_PARAM for a NULL argument or an unknown
+ * form, CGGI_E_UNSUPPORTED for a form the context was made without. */
+int cggi_ctx_transform(const cggi_ctx *ctx, cggi_form_t form, int32_t *width);
 
 /* Message of the last error on the calling thread ("" if none). */
 const char *cggi_last_error(void);

@@ -32,7 +32,8 @@ EXPORTS = ["cggi_params_check", "cggi_ctx_create", "cggi_ctx_destroy",
            "cggi_ctx_latency_mode", "cggi_ctx_latency_groups",
            "cggi_ctx_check", "cggi_ctx_int8_plan", "cggi_ctx_int8_plan_get",
            "cggi_ctx_int8_limits", "cggi_ctx_latency_abort",
-           "cggi_eval_level_noalloc", "cggi_last_error"]
+           "cggi_ctx_transform", "cggi_eval_level_noalloc",
+           "cggi_last_error"]
 
 # INT8 kernel kinds of a plan (cggi_ctx_int8_plan), in the header's order
 KINDS = ("split4", "split2", "tiles1", "tiles2", "tiles4", "split8",
@@ -89,6 +90,7 @@ def lib():
         L.cggi_ctx_int8_plan_get.argtypes = [vp, ip, ip, i32, ip]
         L.cggi_ctx_int8_limits.argtypes = [vp, ip]
         L.cggi_ctx_latency_abort.argtypes = [vp]
+        L.cggi_ctx_transform.argtypes = [vp, ctypes.c_int, ip]
         L.cggi_last_error.restype = ctypes.c_char_p
         for name in EXPORTS[:-1]:
             getattr(L, name).restype = ctypes.c_int
@@ -279,6 +281,14 @@ class Context:
         _check(lib().cggi_ctx_int8_plan_get(self._h, kinds, caps, 8,
                                             ctypes.byref(n)))
         return [(KINDS[kinds[k]], caps[k]) for k in range(n.value)]
+
+    def transform_width(self, form):
+        """The widest batch of the form that now runs on the
+        double-precision kernel (0: none, INT32_MAX: every batch)."""
+        w = ctypes.c_int32()
+        _check(lib().cggi_ctx_transform(self._h, _form(form),
+                                        ctypes.byref(w)))
+        return w.value
 
     def int8_limits(self):
         """{kind name: most bootstraps one launch of it may take} (0 when

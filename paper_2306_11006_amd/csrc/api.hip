@@ -262,14 +262,29 @@ static int64_t scratch_max_gates(const Shape &sh)
     return g;
 }
 
+// Widest batch of a form that calls now run on the FFT kernel.
+static int fft_width(const Ctx *c, cggi_form_t form)
+{
+    if (!c->bsk_fft || (form == CGGI_FORM_INT8 && c->plan_n > 0))
+        return 0;
+    return form == CGGI_FORM_INT8 ? fft_int8_width(c->sh, c->cus) : INT32_MAX;
+}
+
 int form_bootstrap(const Ctx *c, cggi_form_t form, const uint32_t *in,
                    const uint32_t *testv, uint32_t *out, int B,
                    const int32_t *d_count, hipStream_t s)
 {
     const bool i8 = form == CGGI_FORM_INT8;
-    if (!c->bsk_fft || (i8 && c->plan_n > 0))
-        return i8 ? int8_bootstrap(c, in, testv, out, B, d_count, s)
+    const int width = fft_width(c, form);
+    if (width == 0 || (B > width && !d_count))
+        return i8 ? int8_bootstrap(c, in, testv, out, B, d_count, 0, s)
                   : ntt_bootstrap(c, in, testv, out, B, d_count, s);
+    // a count read on the device may be on either side of the width
+    if (B > width) {
+        const int rc = int8_bootstrap(c, in, testv, out, B, d_count, width, s);
+        if (rc)
+            return rc;
+    }
     // INT8 batches that latency mode would take keep its stop rule: they do
     // nothing while the context's error word is set
     int cap = 0;
@@ -280,7 +295,7 @@ int form_bootstrap(const Ctx *c, cggi_form_t form, const uint32_t *in,
             if (kind[k] <= 1 || kind[k] == 5)
                 cap = hi[k];
     }
-    return fft_bootstrap(c, in, testv, out, B, d_count,
+    return fft_bootstrap(c, in, testv, out, B, d_count, width,
                          cap > 0 ? c->x_err : nullptr, cap, s);
 }
 
@@ -614,6 +629,16 @@ int cggi_ctx_int8_plan_get(const cggi_ctx *ctx, int32_t *kinds,
         caps[k] = c0[k];
     }
     *count = n;
+    return CGGI_OK;
+}
+
+int cggi_ctx_transform(const cggi_ctx *ctx, cggi_form_t form, int32_t *width)
+{
+    if (!ctx || !width || (form != CGGI_FORM_NTT && form != CGGI_FORM_INT8))
+        return set_error(CGGI_E_PARAM, "ctx or width NULL, or unknown form");
+    if (!(ctx->forms & (uint32_t)form))
+        return set_error(CGGI_E_UNSUPPORTED, "form not built into the context");
+    *width = fft_width(ctx, form);
     return CGGI_OK;
 }
 

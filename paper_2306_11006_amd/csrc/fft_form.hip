@@ -576,8 +576,8 @@ void k_bootstrap_fft(
     const double *__restrict__ key, const double *__restrict__ tab,
     const uint32_t *__restrict__ in, const uint32_t *__restrict__ testv,
     uint32_t *__restrict__ out, int B, const int32_t *__restrict__ d_count,
-    int pair_width, const uint32_t *__restrict__ stop, int stop_cap, int n,
-    int beta, int l_rt)
+    int pair_width, int width, const uint32_t *__restrict__ stop, int stop_cap,
+    int n, int beta, int l_rt)
 {
     using C = FCfg<N>;
     constexpr int M = C::M, PPL = C::PPL, LPF = C::LPF, FPW = C::FPW;
@@ -600,6 +600,8 @@ void k_bootstrap_fft(
     auto aidx = [](int t) { return H == 2 ? (t & 1) * M + (t >> 1) : t; };
 
     const int count = d_count ? min(B, *d_count) : B;
+    if (count > width)      // the int8 kernels' batch
+        return;
     int from, to;
     fft_share(NB, count, pair_width, &from, &to);
     const int g0 = from + blockIdx.x * NB;
@@ -1074,13 +1076,13 @@ template <int N> int fft_key_t(Ctx *c, const uint32_t *bsk, hipStream_t s)
 
 template <int N, int L>
 int fft_launch_l(const Ctx *c, const uint32_t *in, const uint32_t *testv,
-                 uint32_t *out, int B, const int32_t *d_count,
+                 uint32_t *out, int B, const int32_t *d_count, int width,
                  const uint32_t *stop, int stop_cap, hipStream_t s)
 {
     const Shape &sh = c->sh;
     constexpr int KR = L ? FKR<N>(L) : 1;
     const size_t smem = fft_smem(N, sh.l);
-    int pair_width = 0, grid = B;
+    int pair_width = 0, grid = B < width ? B : width;
     if constexpr (FPAIR<N>(L)) {
         // Batches wider than the chip: two bootstraps per workgroup in
         // rounds of twice the CUs, one per workgroup for a rest of at most
@@ -1096,8 +1098,8 @@ int fft_launch_l(const Ctx *c, const uint32_t *in, const uint32_t *testv,
             hipLaunchKernelGGL((k_bootstrap_fft<N, 2, L, KR, FWPE>),
                                dim3((B + 1) / 2), dim3(FCfg<N>::THREADS),
                                2 * smem, s, c->bsk_fft, c->fft_tw, in, testv,
-                               out, B, d_count, pair_width, stop, stop_cap,
-                               sh.n, sh.beta, sh.l);
+                               out, B, d_count, pair_width, width, stop,
+                               stop_cap, sh.n, sh.beta, sh.l);
             CGGI_HIP_TRY(hipGetLastError());
         }
         if (!ones)
@@ -1105,25 +1107,25 @@ int fft_launch_l(const Ctx *c, const uint32_t *in, const uint32_t *testv,
     }
     hipLaunchKernelGGL((k_bootstrap_fft<N, 1, L, KR, FWPE>), dim3(grid),
                        dim3(FCfg<N>::THREADS), smem, s, c->bsk_fft,
-                       c->fft_tw, in, testv, out, B, d_count, pair_width, stop,
-                       stop_cap, sh.n, sh.beta, sh.l);
+                       c->fft_tw, in, testv, out, B, d_count, pair_width,
+                       width, stop, stop_cap, sh.n, sh.beta, sh.l);
     CGGI_HIP_TRY(hipGetLastError());
     return CGGI_OK;
 }
 
 template <int N>
 int fft_launch(const Ctx *c, const uint32_t *in, const uint32_t *testv,
-               uint32_t *out, int B, const int32_t *d_count,
+               uint32_t *out, int B, const int32_t *d_count, int width,
                const uint32_t *stop, int stop_cap, hipStream_t s)
 {
     return c->sh.l == 3
-               ? fft_launch_l<N, 3>(c, in, testv, out, B, d_count, stop,
-                                    stop_cap, s)
+               ? fft_launch_l<N, 3>(c, in, testv, out, B, d_count, width,
+                                    stop, stop_cap, s)
            : c->sh.l == 2
-               ? fft_launch_l<N, 2>(c, in, testv, out, B, d_count, stop,
-                                    stop_cap, s)
-               : fft_launch_l<N, 0>(c, in, testv, out, B, d_count, stop,
-                                    stop_cap, s);
+               ? fft_launch_l<N, 2>(c, in, testv, out, B, d_count, width,
+                                    stop, stop_cap, s)
+               : fft_launch_l<N, 0>(c, in, testv, out, B, d_count, width,
+                                    stop, stop_cap, s);
 }
 
 } // namespace
@@ -1134,6 +1136,22 @@ double fft_error_bound(const Shape &sh)
     return 2.0 * R * M * std::sqrt(M) * std::ldexp(1.0, sh.beta - 1) *
            32768.0 * (15.0 * m + 2.0 * std::sqrt(2.0) * R) *
            std::ldexp(1.0, -53);
+}
+
+// Widest INT8 batch on this kernel.  At Bg up to 2^7 an int8 GEMM has one
+// digit row per level, and at the small rings its throughput kernels match or
+// beat the transforms once they fill the chip.  64 steps, int8 against this
+// kernel: N = 256, l = 3: 0.388 and 0.301 ms for 1500 bootstraps, 0.413 and
+// 0.464 for 2048, 2.50 and 2.83 for 16384; l = 1: 0.202 and 0.155 for 512,
+// 0.146 and 0.170 for 1024; N = 512, l = 3: 0.855 and 0.786 for 1500, 0.992
+// and 1.030 for 2048; l = 1: 0.246 and 0.172 for 256, 0.313 and 0.382 for
+// 1024.  With two digit rows per level (Bg past 2^7), more levels at N = 512
+// or a larger ring, this kernel is the faster one at every width.
+int fft_int8_width(const Shape &sh, int cus)
+{
+    if (sh.S != 1 || sh.N > 512 || (sh.N == 512 && sh.l > 3))
+        return INT32_MAX;
+    return sh.l > 1 ? 6 * cus : sh.N == 512 ? cus : 2 * cus;
 }
 
 int fft_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s)
@@ -1150,18 +1168,22 @@ int fft_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s)
 }
 
 int fft_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
-                  uint32_t *out, int B, const int32_t *d_count,
+                  uint32_t *out, int B, const int32_t *d_count, int width,
                   const uint32_t *stop, int stop_cap, hipStream_t s)
 {
     switch (c->sh.N) {
     case 256:
-        return fft_launch<256>(c, in, testv, out, B, d_count, stop, stop_cap, s);
+        return fft_launch<256>(c, in, testv, out, B, d_count, width, stop,
+                               stop_cap, s);
     case 512:
-        return fft_launch<512>(c, in, testv, out, B, d_count, stop, stop_cap, s);
+        return fft_launch<512>(c, in, testv, out, B, d_count, width, stop,
+                               stop_cap, s);
     case 1024:
-        return fft_launch<1024>(c, in, testv, out, B, d_count, stop, stop_cap, s);
+        return fft_launch<1024>(c, in, testv, out, B, d_count, width, stop,
+                               stop_cap, s);
     default:
-        return fft_launch<2048>(c, in, testv, out, B, d_count, stop, stop_cap, s);
+        return fft_launch<2048>(c, in, testv, out, B, d_count, width, stop,
+                               stop_cap, s);
     }
 }
 

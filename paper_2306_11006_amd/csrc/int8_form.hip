@@ -1327,13 +1327,15 @@ static int launch_split(const Ctx *c, const uint32_t *in,
 template <int N, int L, int S>
 static int launch_bs_int8_w(const Ctx *c, const uint32_t *in,
                             const uint32_t *testv, uint32_t *out, int B,
-                            const int32_t *d_count, hipStream_t s)
+                            const int32_t *d_count, int lo0, hipStream_t s)
 {
     int32_t kind[8], cap[8];
     const int no = int8_active_plan(c, kind, cap);
-    long lo = 0;
+    long lo = lo0;
     for (int k = 0; k < no; ++k) {
         const long hi = cap[k];
+        if (hi <= lo)
+            continue;
         const bool last = B <= hi || k == no - 1;
         if (!d_count && !last) {
             lo = hi;
@@ -1386,26 +1388,26 @@ static int launch_bs_int8_w(const Ctx *c, const uint32_t *in,
 template <int N>
 static int launch_bs_int8(const Ctx *c, const uint32_t *in,
                           const uint32_t *testv, uint32_t *out, int B,
-                          const int32_t *d_count, hipStream_t s)
+                          const int32_t *d_count, int lo, hipStream_t s)
 {
     const Shape &sh = c->sh;
     // specialised digit loops for the parameter sets in use, generic else
     if (sh.l == 3 && sh.S == 1)
-        return launch_bs_int8_w<N, 3, 1>(c, in, testv, out, B, d_count, s);
+        return launch_bs_int8_w<N, 3, 1>(c, in, testv, out, B, d_count, lo, s);
     if (sh.l == 2 && sh.S == 2)
-        return launch_bs_int8_w<N, 2, 2>(c, in, testv, out, B, d_count, s);
-    return launch_bs_int8_w<N, 0, 0>(c, in, testv, out, B, d_count, s);
+        return launch_bs_int8_w<N, 2, 2>(c, in, testv, out, B, d_count, lo, s);
+    return launch_bs_int8_w<N, 0, 0>(c, in, testv, out, B, d_count, lo, s);
 }
 
 int int8_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
-                   uint32_t *out, int B, const int32_t *d_count,
+                   uint32_t *out, int B, const int32_t *d_count, int lo,
                    hipStream_t s)
 {
     switch (c->sh.N) {
-    case 256: return launch_bs_int8<256>(c, in, testv, out, B, d_count, s);
-    case 512: return launch_bs_int8<512>(c, in, testv, out, B, d_count, s);
-    case 1024: return launch_bs_int8<1024>(c, in, testv, out, B, d_count, s);
-    case 2048: return launch_bs_int8<2048>(c, in, testv, out, B, d_count, s);
+    case 256: return launch_bs_int8<256>(c, in, testv, out, B, d_count, lo, s);
+    case 512: return launch_bs_int8<512>(c, in, testv, out, B, d_count, lo, s);
+    case 1024: return launch_bs_int8<1024>(c, in, testv, out, B, d_count, lo, s);
+    case 2048: return launch_bs_int8<2048>(c, in, testv, out, B, d_count, lo, s);
     default: return set_error(CGGI_E_PARAM, "INT8 form: unsupported N");
     }
 }

@@ -111,17 +111,19 @@ int ntt_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
 // FFT kernel: bound on the error of a coefficient before rounding, key
 // transforms at context creation (a no-op where the bound exceeds 1/4 or
 // the workgroup the LDS), and a launch of B bootstraps (at most *d_count
-// when given).  With `stop`, a launch of at most stop_cap bootstraps does
-// nothing while *stop is set.
+// when given; more than `width` are left to another kernel).  With `stop`, a
+// launch of at most stop_cap bootstraps does nothing while *stop is set.
 double fft_error_bound(const Shape &sh);
+int fft_int8_width(const Shape &sh, int cus);
 int fft_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s);
 int fft_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
-                  uint32_t *out, int B, const int32_t *d_count,
+                  uint32_t *out, int B, const int32_t *d_count, int width,
                   const uint32_t *stop, int stop_cap, hipStream_t s);
 
 int int8_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s);
+// lo: with d_count, only counts above it.
 int int8_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
-                   uint32_t *out, int B, const int32_t *d_count,
+                   uint32_t *out, int B, const int32_t *d_count, int lo,
                    hipStream_t s);
 // Karatsuba kernel (int8_kara.hip): key windows at context creation (a
 // no-op where the kernel is unavailable), and a launch over B bootstraps
@@ -139,7 +141,8 @@ int int8_split_reset(Ctx *c);
 int int8_active_plan(const Ctx *c, int32_t *kind, int32_t *cap);
 
 // Bootstrap B ciphertexts in the given form: the FFT kernel where the
-// context has it and no INT8 plan was set, else the form's own kernels.
+// context has it, no INT8 plan was set and an INT8 batch is not wider than
+// fft_int8_width, else the form's own kernels.
 int form_bootstrap(const Ctx *c, cggi_form_t form, const uint32_t *in,
                    const uint32_t *testv, uint32_t *out, int B,
                    const int32_t *d_count, hipStream_t s);

@@ -18,3 +18,58 @@ def test_run_time_digit_counts(O, p):
     assert F.bound(p) <= 0.25
     F.check(O, p, ("ntt",), 9500 + RUNTIME.index(p), 5, False)
     F.check(O, p, ("ntt",), 9520 + RUNTIME.index(p), 3, True)
+
+
+# (set, int8 bootstraps per CU up to which the transform kernel serves; None:
+# every width)
+WIDTHS = [(F.case(3, 256, 7, 3), 6), (F.case(3, 256, 7, 1), 2),
+          (F.case(2, 512, 7, 2), 6), (F.case(2, 512, 7, 1), 1),
+          (F.case(3, 512, 6, 4), None), (F.case(3, 256, 8, 2), None)]
+
+
+@pytest.mark.parametrize("p,per_cu", WIDTHS, ids=[c[0].name for c in WIDTHS])
+def test_int8_width_of_the_transform_kernel(O, p, per_cu):
+    """The int8 form's batches on both sides of the widest one the transform
+    kernel takes, with a count known on the host and one read on the device."""
+    import numpy as np
+    import torch
+    from paper_2306_11006_amd import cggi, inputs
+    seed = 9600 + p.N + p.l
+    bsk, ksk = inputs.uniform_keys(p, seed)
+    ctx = cggi.Context(p, cggi.to_device(bsk), cggi.to_device(ksk))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    width = ctx.transform_width("int8")
+    assert width == (cggi.INT32_MAX if per_cu is None else per_cu * cus)
+    assert ctx.transform_width("ntt") == cggi.INT32_MAX
+    top = width if per_cu else 2 * cus
+    cts = inputs.uniform_lwe(p, seed + 1, top + 1)
+    with F.cf.ThreadPoolExecutor(F.THREADS) as ex:
+        want = np.stack(list(ex.map(lambda x: O.bootstrap(p, bsk, x), cts)))
+    d_cts = cggi.to_device(cts)
+    for B in (top, top + 1):
+        print(f"width {p.name} B={B}", file=F.sys.stderr, flush=True)
+        out = ctx.bootstrap("int8", d_cts[:B])
+        assert np.array_equal(cggi.to_host(out), want[:B]), B
+    # levels of NAND gates padded with copies: 2G bounds the count from above
+    for B in (top, top + 1):
+        W = 2 * (top + 8)
+        wires = inputs.uniform_lwe(p, seed + 2, W)
+        g = np.zeros((B + 7, 5), dtype=np.int32)
+        g[B:, 0] = cggi.OPCODES["COPY"]
+        g[:, 1] = np.arange(B + 7) % (top // 2)
+        g[:, 2] = top // 2
+        g[:, 4] = W // 2 + np.arange(B + 7)
+        got = {}
+        for form in ("int8", "ntt"):
+            print(f"level {p.name} B={B} form={form}", file=F.sys.stderr,
+                  flush=True)
+            w = cggi.to_device(wires)
+            ctx.eval_level(form, cggi.to_device(g), w)
+            got[form] = cggi.to_host(w)
+        assert np.array_equal(got["int8"], got["ntt"]), B
+        for k in (0, B - 1):
+            pre = O.gate_preop(p.n, "NAND", wires[g[k, 1]], wires[g[k, 2]])
+            out = O.keyswitch(p, ksk, O.bootstrap(p, bsk, pre))
+            assert np.array_equal(got["int8"][g[k, 4]], out), (B, k)
+    ctx.check()
+    ctx.close()
