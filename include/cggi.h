@@ -311,12 +311,16 @@ int cggi_ctx_latency_abort(cggi_ctx *ctx);
  * restores the built-in choice: the double-precision kernel where it serves
  * (see cggi_form_t), else the built-in plan (latency mode with eight, four,
  * then two workgroups while the tiles fit, then 1, 2 or 4 tiles per
- * workgroup by batch width; see cggi_ctx_latency_mode).  While latency mode is off its entries are
- * skipped and their batches go to the next entry.  cggi_ctx_int8_plan_get
- * writes the explicit or the built-in plan (at most max entries; count =
- * entries).  Host state only: affects calls made afterwards.  Errors: CGGI_E_PARAM for a NULL
- * ctx or an invalid plan (nothing changes), CGGI_E_UNSUPPORTED without the
- * INT8 form, CGGI_E_SHAPE when max is too small. */
+ * workgroup by batch width; see cggi_ctx_latency_mode).  While latency mode
+ * is off its entries are skipped and their batches go to the next entry.
+ * cggi_ctx_int8_plan_get writes the explicit or the built-in plan (at most max
+ * entries; count = entries), and setting what it wrote changes nothing: where
+ * the double-precision kernel serves, the built-in plan, with or without its
+ * latency-mode entries, stands for the built-in choice (with a last cap other
+ * than INT32_MAX it is an explicit plan).  Host state only: affects calls made
+ * afterwards.  Errors: CGGI_E_PARAM for a NULL ctx or an invalid plan (nothing
+ * changes), CGGI_E_UNSUPPORTED without the INT8 form, CGGI_E_SHAPE when max is
+ * too small. */
 enum {
     CGGI_K_SPLIT4 = 0,
     CGGI_K_SPLIT2 = 1,

@@ -603,6 +603,12 @@ int cggi_ctx_int8_plan(cggi_ctx *ctx, const int32_t *kinds,
     if (caps[count - 1] < (1 << 24))
         return set_error(CGGI_E_PARAM, "the last plan entry must hold every "
                                        "batch (cap >= 2^24)");
+    // Where the FFT kernel serves, cggi_ctx_int8_plan_get writes the built-in
+    // plan for its choice: setting that again has to change nothing.
+    if (ctx->bsk_fft && int8_plan_is_builtin(ctx, kinds, caps, count)) {
+        ctx->plan_n = 0;
+        return CGGI_OK;
+    }
     for (int k = 0; k < count; ++k) {
         ctx->plan_kind[k] = kinds[k];
         ctx->plan_cap[k] = caps[k];

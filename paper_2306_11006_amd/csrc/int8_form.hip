@@ -1220,55 +1220,84 @@ static int make_key_n(Ctx *c, const uint32_t *bsk, hipStream_t s)
     return CGGI_OK;
 }
 
+static bool latency_kind(int32_t kind)
+{
+    return kind <= 1 || kind == 5;
+}
+
+// The built-in plan: latency mode with eight workgroups per tile up to half
+// their limit (beyond that their longer exchange outweighs the shorter K loop:
+// 2.87 vs 3.05 ms at 1 bootstrap, 3.48 vs 3.25 ms at 32, N = 1024), four, then
+// two while the tiles fit; then the fewest tiles per workgroup that still fit
+// the batch into one wave of workgroups over the CUs.
+static int builtin_plan(const Ctx *c, int32_t *kind, int32_t *cap)
+{
+    int n = 0;
+    const int64_t gpt = c->sh.N <= 1024 ? 1024 / c->sh.N : 1;
+    if (c->kind_limit[5] > 1) {
+        kind[n] = 5;
+        cap[n++] = (int32_t)(c->kind_limit[5] / 2);
+    }
+    if (c->kind_limit[0] > c->kind_limit[5] / 2) {
+        kind[n] = 0;
+        cap[n++] = (int32_t)c->kind_limit[0];
+    }
+    if (c->kind_limit[1] > c->kind_limit[0]) {
+        kind[n] = 1;
+        cap[n++] = (int32_t)c->kind_limit[1];
+    }
+    if (c->kind_limit[2] > 0) {
+        kind[n] = 2;
+        cap[n++] = (int32_t)(c->cus * gpt);
+        kind[n] = 3;
+        cap[n++] = (int32_t)(2 * c->cus * gpt);
+    }
+    // the widest batches: the Karatsuba kernel where it is available
+    // (3/4 of the MFMA work; 9% faster at 1024 default bootstraps)
+    kind[n] = c->kind_limit[6] > 0 ? 6 : 4;
+    cap[n++] = INT32_MAX;
+    return n;
+}
+
 int int8_active_plan(const Ctx *c, int32_t *kind, int32_t *cap)
 {
     int32_t k0[8], c0[8];
-    int n0 = 0;
-    if (c->plan_n > 0) {
-        for (int k = 0; k < c->plan_n; ++k) {
+    int n0 = c->plan_n;
+    if (n0 > 0) {
+        for (int k = 0; k < n0; ++k) {
             k0[k] = c->plan_kind[k];
             c0[k] = c->plan_cap[k];
         }
-        n0 = c->plan_n;
     } else {
-        // built-in: latency mode with eight workgroups per tile up to half
-        // their limit (beyond that their longer exchange outweighs the
-        // shorter K loop: 2.87 vs 3.05 ms at 1 bootstrap, 3.48 vs 3.25 ms
-        // at 32, N = 1024), four, then two while the tiles fit; then the
-        // fewest tiles per workgroup that still fit the batch into one wave
-        // of workgroups over the CUs
-        const int64_t gpt = c->sh.N <= 1024 ? 1024 / c->sh.N : 1;
-        if (c->kind_limit[5] > 1) {
-            k0[n0] = 5;
-            c0[n0++] = (int32_t)(c->kind_limit[5] / 2);
-        }
-        if (c->kind_limit[0] > c->kind_limit[5] / 2) {
-            k0[n0] = 0;
-            c0[n0++] = (int32_t)c->kind_limit[0];
-        }
-        if (c->kind_limit[1] > c->kind_limit[0]) {
-            k0[n0] = 1;
-            c0[n0++] = (int32_t)c->kind_limit[1];
-        }
-        if (c->kind_limit[2] > 0) {
-            k0[n0] = 2;
-            c0[n0++] = (int32_t)(c->cus * gpt);
-            k0[n0] = 3;
-            c0[n0++] = (int32_t)(2 * c->cus * gpt);
-        }
-        // the widest batches: the Karatsuba kernel where it is available
-        // (3/4 of the MFMA work; 9% faster at 1024 default bootstraps)
-        k0[n0] = c->kind_limit[6] > 0 ? 6 : 4;
-        c0[n0++] = INT32_MAX;
+        n0 = builtin_plan(c, k0, c0);
     }
     int n = 0;
     for (int k = 0; k < n0; ++k) {
-        if (!c->split_on && (k0[k] <= 1 || k0[k] == 5))
+        if (!c->split_on && latency_kind(k0[k]))
             continue;          // its batches go to the next entry
         kind[n] = k0[k];
         cap[n++] = c0[k];
     }
     return n;
+}
+
+bool int8_plan_is_builtin(const Ctx *c, const int32_t *kind,
+                          const int32_t *cap, int count)
+{
+    int32_t k0[8], c0[8];
+    const int n0 = builtin_plan(c, k0, c0);
+    for (int latency = 0; latency < 2; ++latency) {
+        int n = 0;
+        bool same = true;
+        for (int k = 0; k < n0; ++k)
+            if (latency || !latency_kind(k0[k])) {
+                same = same && n < count && kind[n] == k0[k] && cap[n] == c0[k];
+                ++n;
+            }
+        if (same && n == count)
+            return true;
+    }
+    return false;
 }
 
 int int8_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s)

@@ -139,6 +139,9 @@ int int8_split_reset(Ctx *c);
 // latency-mode entries dropped while latency mode is off.  Returns the
 // number of entries (at most 8).
 int int8_active_plan(const Ctx *c, int32_t *kind, int32_t *cap);
+// Whether a plan is the built-in one, with or without its latency-mode entries.
+bool int8_plan_is_builtin(const Ctx *c, const int32_t *kind,
+                          const int32_t *cap, int count);
 
 // Bootstrap B ciphertexts in the given form: the FFT kernel where the
 // context has it, no INT8 plan was set and an INT8 batch is not wider than

@@ -117,11 +117,14 @@ def cache_dir():
 
 
 def _force(ctx, kind, limits):
-    """Plan that sends every batch within the kind's limit to `kind`."""
+    """Plan that sends every batch within the kind's limit to `kind` (its
+    last cap, the widest batch, keeps it apart from a built-in plan of one
+    entry)."""
+    top = 1 << 24
     if kind.startswith("split"):
-        ctx.int8_plan([(kind, limits[kind]), ("tiles4", MAX_CAP)])
+        ctx.int8_plan([(kind, limits[kind]), ("tiles4", top)])
     else:
-        ctx.int8_plan([(kind, MAX_CAP)])
+        ctx.int8_plan([(kind, top)])
 
 
 def _time(ctx, form, x, out, reps):
