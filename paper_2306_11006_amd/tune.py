@@ -10,10 +10,11 @@ cggi_bootstrap_batch per measurement under a plan that forces the kernel,
 HIP events around the launch), keeps the fastest per width, and compresses
 the winners into a plan of (kind, cap) entries: entry k takes the batches
 of cap[k-1] + 1 .. cap[k] bootstraps, so a width between two grid points
-goes to the kernel that won the larger one.  It also times the NTT form per
-width, so a caller can pick the faster form per level (best_form; the NTT
-form wins wherever the double-precision transform serves it, while an
-installed plan keeps the int8 form on the kernels above).
+goes to the kernel that won the larger one.  Where the double-precision
+transform serves the int8 form, which no entry of a plan can name, its
+built-in choice is timed as well and is the table's plan unless the kernels
+above are faster over the grid.  The tuner also times the NTT form per width,
+so a caller can pick the faster form per level (best_form).
 
 Tables are cached as JSON keyed by parameter set, device, CU count and the
 library build (cache directory: $CGGI_TUNE_CACHE, else ~/.cache/cggi_tune).
@@ -27,6 +28,7 @@ import argparse
 import bisect
 import hashlib
 import json
+import math
 import os
 
 import torch
@@ -88,6 +90,16 @@ def plan_from_winners(winners, max_entries=MAX_ENTRIES):
     return plan
 
 
+def pick_plan(winners, best, served, built_in):
+    """(plan, {width: ms}) of the int8 form: the built-in plan where what it
+    stands for, timed in `served`, is at least as fast over the grid
+    (geometric mean) as each width's winner, timed in `best`; else, or with no
+    such times, the plan from the winners."""
+    if served and sum(math.log(served[w] / best[w]) for w in best) <= 0.0:
+        return list(built_in), served
+    return plan_from_winners(winners), best
+
+
 def best_form(table, bootstraps):
     """'int8' or 'ntt', whichever the table timed faster at the smallest grid
     width holding `bootstraps` (the largest width beyond the grid)."""
@@ -145,11 +157,13 @@ def _time(ctx, form, x, out, reps):
 
 def autotune(ctx, p, widths=None, reps=3, time_ntt=True, seed=1,
              max_width=4096):
-    """Time every int8 kernel (and the NTT form) per width; return the table
-    {"plan": [(kind, cap)], "times": {w: {kind: ms}}, "forms": {w: {form:
-    ms}}, ...}.  Every timed kernel's outputs must equal those of the first
-    one timed at that width (the NTT form when the context has it), else
-    RuntimeError.  The context's plan is restored to the built-in one."""
+    """Time every int8 kernel (and the NTT form, and the built-in choice where
+    the double-precision transform serves) per width; return the table
+    {"plan": [(kind, cap)], "times": {w: {kind: ms}}, "served": {w: ms},
+    "forms": {w: {form: ms}}, ...}.  Every timed kernel's outputs must equal
+    those of the first one timed at that width (the NTT form when the context
+    has it), else RuntimeError.  The context's plan is restored to the built-in
+    one."""
     limits = ctx.int8_limits()
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     gpt = 1024 // p.N if p.N <= 1024 else 1
@@ -160,7 +174,10 @@ def autotune(ctx, p, widths=None, reps=3, time_ntt=True, seed=1,
     out = torch.empty((max(widths), p.N + 1), dtype=torch.int32,
                       device=cts.device)
     has_ntt = time_ntt and "ntt" in ctx.forms
-    times, forms, winners = {}, {}, []
+    times, forms, winners, best_ms, served = {}, {}, [], {}, {}
+    ctx.int8_plan(None)
+    built_in = ctx.int8_plan_get()
+    transform = ctx.transform_width("int8") > 0
     try:
         for w in widths:
             x = cts[:w]
@@ -170,27 +187,38 @@ def autotune(ctx, p, widths=None, reps=3, time_ntt=True, seed=1,
                 f["ntt"] = round(_time(ctx, "ntt", x, out[:w], reps), 4)
                 ref = out[:w].clone()
             row = {}
-            for kind in cggi.KINDS:
-                if limits[kind] < w:
+            for kind in (None,) * transform + cggi.KINDS:
+                if kind is None:
+                    ctx.int8_plan(None)
+                elif limits[kind] < w:
                     continue
-                _force(ctx, kind, limits)
-                row[kind] = round(_time(ctx, "int8", x, out[:w], reps), 4)
+                else:
+                    _force(ctx, kind, limits)
+                t = round(_time(ctx, "int8", x, out[:w], reps), 4)
+                if kind is None:
+                    served[str(w)] = t
+                else:
+                    row[kind] = t
                 if ref is None:
                     ref = out[:w].clone()
                 elif not torch.equal(out[:w], ref):
-                    raise RuntimeError(f"tune: kernel {kind} at width {w} "
-                                       "disagrees with the reference outputs")
+                    raise RuntimeError(f"tune: kernel {kind or 'built-in'} at "
+                                       f"width {w} disagrees with the "
+                                       "reference outputs")
             best = min(row, key=row.get)
             winners.append((w, best))
             times[str(w)] = row
-            f["int8"] = row[best]
+            best_ms[str(w)] = row[best]
             forms[str(w)] = f
     finally:
         ctx.int8_plan(None)
+    plan, int8_ms = pick_plan(winners, best_ms, served, built_in)
+    for w, f in forms.items():
+        f["int8"] = int8_ms[w]
     return {"params": p.name, "device": torch.cuda.get_device_name(0),
             "cus": cus, "limits": limits, "widths": widths, "reps": reps,
-            "times": times, "forms": forms, "checked": True,
-            "plan": plan_from_winners(winners)}
+            "times": times, "served": served, "forms": forms,
+            "checked": True, "plan": plan}
 
 
 def apply(ctx, table):
@@ -242,6 +270,7 @@ def main(argv=None):
                       "limits": table["limits"]}))
     for w in table["widths"]:
         print(json.dumps({"width": w, "int8": table["times"][str(w)],
+                          "built_in": table["served"].get(str(w)),
                           "forms": table["forms"][str(w)]}))
     ctx.close()
 
