@@ -115,6 +115,13 @@ int cggi_ctx_create(const cggi_params_t *params, const uint32_t *d_bsk,
                     const uint32_t *d_ksk, uint32_t forms, void *stream,
                     cggi_ctx **out);
 
+/* cggi_ctx_create without the key's double-precision transforms: every form
+ * runs on its own kernels, as in a context of cggi_ctx_create whose transforms
+ * find no room in memory.  Bit-identical results, less memory, slower. */
+int cggi_ctx_create_no_transform(const cggi_params_t *params,
+                                 const uint32_t *d_bsk, const uint32_t *d_ksk,
+                                 uint32_t forms, void *stream, cggi_ctx **out);
+
 /* Free a context and everything it allocated (waits for the device).
  * NULL is accepted. */
 int cggi_ctx_destroy(cggi_ctx *ctx);

@@ -24,7 +24,8 @@ E_PARAM, E_SHAPE, E_ALIAS, E_HIP, E_NOMEM, E_UNSUPPORTED, E_TIMEOUT = \
 OPCODES = {"NAND": 0, "AND": 1, "OR": 2, "XOR": 3, "MUX": 4, "NOT": 5,
            "COPY": 6, "CONST0": 7, "CONST1": 8, "NOR": 9, "XNOR": 10}
 
-EXPORTS = ["cggi_params_check", "cggi_ctx_create", "cggi_ctx_destroy",
+EXPORTS = ["cggi_params_check", "cggi_ctx_create",
+           "cggi_ctx_create_no_transform", "cggi_ctx_destroy",
            "cggi_ctx_reserve", "cggi_bootstrap_batch", "cggi_keyswitch_batch",
            "cggi_eval_level", "cggi_levelize", "cggi_ctx_profile",
            "cggi_ctx_profile_read", "cggi_measure_int8_mfma",
@@ -66,9 +67,9 @@ def lib():
         L = ctypes.CDLL(LIB_PATH)
         vp, i32 = ctypes.c_void_p, ctypes.c_int32
         L.cggi_params_check.argtypes = [ctypes.POINTER(Params)]
-        L.cggi_ctx_create.argtypes = [ctypes.POINTER(Params), vp, vp,
-                                      ctypes.c_uint32, vp,
-                                      ctypes.POINTER(vp)]
+        for f in (L.cggi_ctx_create, L.cggi_ctx_create_no_transform):
+            f.argtypes = [ctypes.POINTER(Params), vp, vp, ctypes.c_uint32, vp,
+                          ctypes.POINTER(vp)]
         L.cggi_ctx_destroy.argtypes = [vp]
         L.cggi_ctx_reserve.argtypes = [vp, i32]
         L.cggi_bootstrap_batch.argtypes = [vp, ctypes.c_int, vp, vp, vp, i32,
@@ -196,9 +197,12 @@ def _form(form):
 
 
 class Context:
-    """A cggi_ctx: derived key forms for one parameter set on one GPU."""
+    """A cggi_ctx: derived key forms for one parameter set on one GPU.
+    transform=False: without the key's double-precision transforms (the forms
+    run on their own kernels)."""
 
-    def __init__(self, params, bsk, ksk, forms=("ntt", "int8"), stream=None):
+    def __init__(self, params, bsk, ksk, forms=("ntt", "int8"), stream=None,
+                 transform=True):
         self.params = params
         self.forms = tuple(forms)
         self._ksk = ksk          # the library keeps a pointer to it
@@ -209,9 +213,10 @@ class Context:
         _numel(ksk, "ksk", params.ksk_shape)
         self._ps = params_struct(params)
         h = ctypes.c_void_p()
-        _check(lib().cggi_ctx_create(ctypes.byref(self._ps), _ptr(bsk),
-                                     _ptr(ksk), mask, _stream(stream),
-                                     ctypes.byref(h)))
+        create = (lib().cggi_ctx_create if transform
+                  else lib().cggi_ctx_create_no_transform)
+        _check(create(ctypes.byref(self._ps), _ptr(bsk), _ptr(ksk), mask,
+                      _stream(stream), ctypes.byref(h)))
         self._h = h
 
     def close(self):

@@ -363,9 +363,9 @@ static int make_keys(Ctx *c, const uint32_t *bsk, bool fft, hipStream_t s)
     return CGGI_OK;
 }
 
-int cggi_ctx_create(const cggi_params_t *params, const uint32_t *d_bsk,
-                    const uint32_t *d_ksk, uint32_t forms, void *stream,
-                    cggi_ctx **out)
+static int ctx_create(const cggi_params_t *params, const uint32_t *d_bsk,
+                      const uint32_t *d_ksk, uint32_t forms, bool transform,
+                      void *stream, cggi_ctx **out)
 {
     if (!out)
         return set_error(CGGI_E_SHAPE, "out is NULL");
@@ -384,7 +384,7 @@ int cggi_ctx_create(const cggi_params_t *params, const uint32_t *d_bsk,
                                        "4-byte aligned");
     hipStream_t s = (hipStream_t)stream;
     // where the other keys don't fit beside the FFT kernel's, without it
-    for (int fft = 1; fft >= 0; --fft) {
+    for (int fft = transform; fft >= 0; --fft) {
         cggi_ctx *c = new cggi_ctx();
         c->p = *params;
         c->sh = sh;
@@ -403,6 +403,20 @@ int cggi_ctx_create(const cggi_params_t *params, const uint32_t *d_bsk,
         (void)hipGetLastError();
     }
     return rc;
+}
+
+int cggi_ctx_create(const cggi_params_t *params, const uint32_t *d_bsk,
+                    const uint32_t *d_ksk, uint32_t forms, void *stream,
+                    cggi_ctx **out)
+{
+    return ctx_create(params, d_bsk, d_ksk, forms, true, stream, out);
+}
+
+int cggi_ctx_create_no_transform(const cggi_params_t *params,
+                                 const uint32_t *d_bsk, const uint32_t *d_ksk,
+                                 uint32_t forms, void *stream, cggi_ctx **out)
+{
+    return ctx_create(params, d_bsk, d_ksk, forms, false, stream, out);
 }
 
 int cggi_ctx_destroy(cggi_ctx *ctx)
