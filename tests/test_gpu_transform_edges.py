@@ -73,3 +73,58 @@ def test_int8_width_of_the_transform_kernel(O, p, per_cu):
             assert np.array_equal(got["int8"][g[k, 4]], out), (B, k)
     ctx.check()
     ctx.close()
+
+
+@pytest.mark.parametrize("B", [257, 600])
+def test_two_bootstraps_per_workgroup_at_two_levels(O, B):
+    F.check(O, F.case(4, 1024, 10, 2), ("ntt",), 9700 + B, B, False)
+
+
+@pytest.mark.parametrize("p", F.INSIDE + F.PAST,
+                         ids=[p.name for p in F.INSIDE + F.PAST])
+def test_which_kernel_serves(p):
+    from paper_2306_11006_amd import cggi, inputs
+    bsk, ksk = inputs.uniform_keys(p, 9750)
+    ctx = cggi.Context(p, cggi.to_device(bsk), cggi.to_device(ksk),
+                       forms=("ntt",))
+    assert ctx.transform_width("ntt") == (cggi.INT32_MAX if p in F.INSIDE
+                                          else 0)
+    ctx.close()
+
+
+@pytest.mark.parametrize("l", [2, 3])
+def test_device_counts_around_the_pairs(O, l):
+    """Levels whose bootstrap count, known on the device only, fills rounds of
+    two bootstraps per workgroup and leaves a rest on either side of half a
+    round (MUX gates: two bootstraps each)."""
+    import numpy as np
+    import torch
+    from paper_2306_11006_amd import cggi, inputs
+    p = F.case(4, 1024, 7, l)
+    bsk, ksk = inputs.uniform_keys(p, 9760 + l)
+    ctx = cggi.Context(p, cggi.to_device(bsk), cggi.to_device(ksk))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for count in (1, cus, cus + 1, 2 * cus, 2 * cus + 1, 3 * cus,
+                  3 * cus + 1):
+        mux = min(count // 2, 40)
+        G = count - mux + 5                     # and five copies
+        wires = inputs.uniform_lwe(p, 9770 + count, 64 + G)
+        g = inputs.rng(9780 + count).integers(0, 64, size=(G, 5))
+        g[:, 0] = cggi.OPCODES["NAND"]
+        g[:mux, 0] = cggi.OPCODES["MUX"]
+        g[-5:, 0] = cggi.OPCODES["COPY"]
+        g[:, 4] = 64 + np.arange(G)
+        g = g.astype(np.int32)
+        with F.cf.ThreadPoolExecutor(F.THREADS) as ex:
+            want = np.stack(list(ex.map(
+                lambda t: O.gate(p, int(t[0]), bsk, ksk, wires[t[1]],
+                                 wires[t[2]], wires[t[3]]), g)))
+        for form in ("int8", "ntt"):
+            print(f"level {p.name} count={count} form={form}",
+                  file=F.sys.stderr, flush=True)
+            w = cggi.to_device(wires)
+            ctx.eval_level(form, cggi.to_device(g), w)
+            got = cggi.to_host(w)
+            assert np.array_equal(got[64:], want), (count, form)
+            assert np.array_equal(got[:64], wires[:64])
+    ctx.close()
