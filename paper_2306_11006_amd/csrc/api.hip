@@ -123,10 +123,8 @@ static void free_ctx(Ctx *c)
     (void)hipFree(c->corr_i8);
     (void)hipFree(c->bsk_k8);
     (void)hipFree(c->corr_k8);
-    for (int v = 0; v < 3; ++v) {
+    for (int v = 0; v < 3; ++v)
         (void)hipFree(c->x_buf[v]);
-        (void)hipFree(c->x_epoch[v]);
-    }
     (void)hipFree(c->x_err);
     if (c->abort_stream)
         (void)hipStreamDestroy(c->abort_stream);

@@ -1053,10 +1053,11 @@ template <int N> int fft_key_t(Ctx *c, const uint32_t *bsk, hipStream_t s)
 {
     using C = FCfg<N>;
     const Shape &sh = c->sh;
-    c->fft_tab = fft_table<N>();
+    // made once; the upload below reads it after this function has returned
+    static const std::vector<double> host_tab = fft_table<N>();
     const int npoly = sh.n * 2 * sh.l * 4;
     const size_t words = (size_t)npoly * C::M * 2;
-    const size_t tab = c->fft_tab.size() * sizeof(double);
+    const size_t tab = host_tab.size() * sizeof(double);
     if (hipMalloc(&c->bsk_fft, words * sizeof(double) + tab) != hipSuccess) {
         // the context then serves its forms with their own kernels
         (void)hipGetLastError();
@@ -1064,7 +1065,7 @@ template <int N> int fft_key_t(Ctx *c, const uint32_t *bsk, hipStream_t s)
         return CGGI_OK;
     }
     c->fft_tw = c->bsk_fft + words;
-    CGGI_HIP_TRY(hipMemcpyAsync(c->fft_tw, c->fft_tab.data(), tab,
+    CGGI_HIP_TRY(hipMemcpyAsync(c->fft_tw, host_tab.data(), tab,
                                 hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_fft_key<N>, dim3((npoly + C::FPW - 1) / C::FPW),
                        dim3(64), 0, s, bsk, c->fft_tw, c->bsk_fft, npoly);

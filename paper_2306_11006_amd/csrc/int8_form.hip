@@ -1082,12 +1082,12 @@ static int split_setup_g(Ctx *c, int v, hipStream_t s)
     if (groups < 1)
         return CGGI_OK;
     const size_t xwords = (size_t)groups * 2 * G * SplitCfg<N>::WORDS;
-    if (hipMalloc(&c->x_buf[v], xwords * 8) != hipSuccess ||
-        hipMalloc(&c->x_epoch[v], (size_t)groups * 4) != hipSuccess)
+    const size_t bytes = xwords * 8 + (size_t)groups * 4;
+    if (hipMalloc(&c->x_buf[v], bytes) != hipSuccess)
         return set_error(CGGI_E_NOMEM, "hipMalloc of the latency-mode "
                                        "exchange buffers failed");
-    CGGI_HIP_TRY(hipMemsetAsync(c->x_buf[v], 0, xwords * 8, s));
-    CGGI_HIP_TRY(hipMemsetAsync(c->x_epoch[v], 0, (size_t)groups * 4, s));
+    CGGI_HIP_TRY(hipMemsetAsync(c->x_buf[v], 0, bytes, s));
+    c->x_epoch[v] = reinterpret_cast<uint32_t *>(c->x_buf[v] + xwords);
     c->x_words[v] = xwords;
     c->split_groups[v] = groups;
     return CGGI_OK;

@@ -40,7 +40,6 @@ struct cggi_ctx {
     // bound does not prove the rounding
     double *bsk_fft = nullptr;    // [n][2l][4][N/2] complex, key halves
     double *fft_tw = nullptr;     // its twiddle table, in the same allocation
-    std::vector<double> fft_tab;  // the table's host copy (its upload's source)
     // INT8 form
     int8_t *bsk_i8 = nullptr;     // [n][R][2][4][elen] limb windows
     uint32_t *corr_i8 = nullptr;  // [n][2][N] digit-offset correction (N <= 1024)
@@ -54,7 +53,7 @@ struct cggi_ctx {
     int split_groups[3] = {0, 0, 0}; // most tile groups per launch (0: none)
     unsigned long long *x_buf[3] = {}; // [groups][2][G][1024]
     size_t x_words[3] = {0, 0, 0};
-    uint32_t *x_epoch[3] = {};    // [groups] launch epochs
+    uint32_t *x_epoch[3] = {};    // [groups] launch epochs (behind x_buf)
     uint32_t *x_err = nullptr;    // [1] set when a member's wait timed out
     hipStream_t abort_stream = nullptr; // non-blocking, for latency_abort
     // INT8 kernel plan (cggi_ctx_int8_plan): entry k runs the batches of

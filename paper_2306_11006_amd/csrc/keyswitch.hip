@@ -180,41 +180,47 @@ constexpr int KSM_THREADS = 512;   // eight waves
 // byte e of lane l in block (nt, j, sj, q) is limb q of
 // ksk[j][p][h][32 nt + (l & 31)] for slot 32 sj + 16 (l >> 5) + e = p 2^gamma
 // + h, zero where p >= t or the column is past n.  Limbs are signed:
-// v = sum_q 2^(8q) v_q with v_q in [-128, 127].
+// v = sum_q 2^(8q) v_q with v_q in [-128, 127].  A wave per (nt, j, sj): a lane
+// reads its 16 key words once (32 columns side by side) and writes its 16
+// bytes of each limb; a thread per dword, which read every word for each limb,
+// took 143 us at the default set and 657 us at the large one, this 53 and 182.
 __global__ __launch_bounds__(256) void k_ksk_to_i8(
     const uint32_t *__restrict__ ksk, uint32_t *__restrict__ out, int n,
     int N, int t, int gamma, int ksj, int nt_tiles)
 {
-    const size_t total = (size_t)nt_tiles * N * ksj * 4 * 256;   // dwords
+    const int lane = threadIdx.x & 63;
+    const int blk = __builtin_amdgcn_readfirstlane(
+        (int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (blk >= nt_tiles * N * ksj)
+        return;
     const int base = 1 << gamma;
-    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-         idx < total; idx += (size_t)gridDim.x * blockDim.x) {
-        const int dw = (int)(idx & 255);
-        size_t b = idx >> 8;
-        const int q = (int)(b & 3);
-        b >>= 2;
-        const int sj = (int)(b % ksj);
-        b /= ksj;
-        const int j = (int)(b % N);
-        const int nt = (int)(b / N);
-        const int lane = dw >> 2, e4 = dw & 3;
-        const int col = 32 * nt + (lane & 31), kh = lane >> 5;
-        uint32_t word = 0;
+    const int sj = blk % ksj, j = blk / ksj % N, nt = blk / ksj / N;
+    const int col = 32 * nt + (lane & 31), kh = lane >> 5;
+    const uint32_t *row = ksk + (size_t)j * t * base * (n + 1) + col;
+    uint32_t w[4][4];                // [limb][dword of four slots]
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) {
+        uint32_t v[4];
+#pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int slot = 32 * sj + 16 * kh + 4 * e4 + e;
-            const int p = slot >> gamma, h = slot & (base - 1);
-            uint32_t v = 0;
-            if (p < t && col <= n)
-                v = ksk[(((size_t)j * t + p) * base + h) * (n + 1) + col];
-            int8_t limb = 0;
-            for (int k = 0; k <= q; ++k) {
-                limb = (int8_t)(v & 0xFFu);
-                v = (v - (uint32_t)(int32_t)limb) >> 8;
-            }
-            word |= (uint32_t)(uint8_t)limb << (8 * e);
+            const int slot = 32 * sj + 16 * kh + 4 * e4 + e;   // p 2^gamma + h
+            const bool in = slot < t * base && col <= n;
+            // the low three limbs plus 128 are the bytes of v + 0x808080
+            v[e] = ((in ? row[(size_t)slot * (n + 1)] : 0u) + 0x808080u) ^
+                   0x808080u;
         }
-        out[idx] = word;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            w[q][e4] = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                w[q][e4] |= (v[e] >> (8 * q) & 0xFFu) << (8 * e);
+        }
     }
+    uint4 *dst = reinterpret_cast<uint4 *>(out) + (size_t)blk * 256 + lane;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        dst[q * 64] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
 }
 
 // out rows = (0, .., 0, b'): the GEMM then subtracts into them.
@@ -588,7 +594,8 @@ int keyswitch_make_key(Ctx *c, hipStream_t s)
                            : ks_mfma_attrs<0>();
     if (rc)
         return rc;
-    hipLaunchKernelGGL(k_ksk_to_i8, dim3(4096), dim3(256), 0, s, c->ksk,
+    hipLaunchKernelGGL(k_ksk_to_i8, dim3((nt_tiles * sh.N * ksj + 3) / 4),
+                       dim3(256), 0, s, c->ksk,
                        reinterpret_cast<uint32_t *>(c->ksk_i8), sh.n, sh.N,
                        sh.t, sh.gamma, ksj, nt_tiles);
     CGGI_HIP_TRY(hipGetLastError());
