@@ -525,10 +525,16 @@ int ks_mfma_dispatch(const Ctx *c, const uint32_t *in, uint32_t *out, int B,
     hipLaunchKernelGGL(k_ks_init<LEVEL>, dim3(init_blocks), dim3(256), 0, s,
                        in, out, B, lv, sh.n, sh.N);
     CGGI_HIP_TRY(hipGetLastError());
-    // four row tiles from two on: 64 default ciphertexts 25.5 us against 28.0
-    // with two; 37 take 24.0 against 23.3, 1 takes 22.3 against 17.5
-    return B > 48 ? ks_mfma_launch<4, LEVEL>(c, in, out, B, lv, s)
-                  : ks_mfma_launch<2, LEVEL>(c, in, out, B, lv, s);
+    // Four row tiles past 64 ciphertexts, where two would read the key again.
+    // From 49 on already where a long j range at few slot blocks per j hides
+    // the empty tiles: 64 ciphertexts at n = 630, N = 1024 take 23.8 us in four
+    // tiles and 27.8 in two with one block, 34.3 and 37.6 with two, but 77.2
+    // and 70.5 with four blocks; at n = 742, N = 2048 38.8 and 42.1 with one,
+    // 86.0 and 83.0 with two; at N = 256 14.7 and 11.9 with one.
+    const bool four = B > 64 || (B > 48 && sh.N >= 1024 &&
+                                 sh.N * c->ks_ksj <= 2048);
+    return four ? ks_mfma_launch<4, LEVEL>(c, in, out, B, lv, s)
+                : ks_mfma_launch<2, LEVEL>(c, in, out, B, lv, s);
 }
 
 template <bool LEVEL>
