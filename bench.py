@@ -9,7 +9,9 @@ gate, writing the 1024 output wires.  Inputs and keys are resident in HBM
 before timing starts.  The int8 form gives `value`; the NTT form is timed on
 the same batch and reported beside it.  Both run on the double-precision
 transform kernel at these parameters; `int8_gemm` times the int8-MFMA kernels
-on the same batch, under an explicit plan.  Each form's step is also captured
+on the same batch, under an explicit plan, and `ntt_modular` the modular NTT
+kernel, in a context without the transform key; their outputs have to be the
+same (`forms_bit_identical`).  Each form's step is also captured
 once as a HIP graph and replayed `steps` times (`graph_replay`: mean and
 median per replay, and whether the replays reproduce the eager outputs).
 
@@ -482,6 +484,22 @@ def main():
         ctx.int8_plan(None)
         gemm["same"] = bool(np.array_equal(gemm_out, outs["int8"]))
         log(f"[bench] int8 GEMM kernels: {gemm['ms_per_step']:.3f} ms/step")
+    modular = None
+    if fft and "ntt" in res:
+        # the NTT form's own kernel on the same batch: a context without the
+        # transform key
+        own = cggi.Context(p, cggi.to_device(bsk, dev),
+                           cggi.to_device(ksk, dev), forms=("ntt",),
+                           transform=False)
+        own.reserve(G)
+        modular, modular_out = time_level(own, "ntt", gates, wires,
+                                          args.steps, args.warmup,
+                                          out_rows=slice(2 * G, 3 * G),
+                                          bootstraps=G)
+        own.close()
+        modular["same"] = bool(np.array_equal(modular_out, outs["ntt"]))
+        log(f"[bench] modular NTT kernel: {modular['ms_per_step']:.3f} "
+            "ms/step")
     if fft:
         roof = fft_roof(r, G)
         roof.update({
@@ -549,7 +567,15 @@ def main():
             "ms_per_step": round(gemm["ms_per_step"], 4),
             "graph_replay": gemm["graph"], "roofline": gemm_roof,
             "outputs_equal_value": gemm["same"]}
-    line["forms_bit_identical"] = bool(forms_agree)
+    if modular:
+        line["ntt_modular"] = {
+            "value": round(modular["bootstraps_per_s"], 1),
+            "ms_per_step": round(modular["ms_per_step"], 4),
+            "graph_replay": modular["graph"], "roofline": ntt_roof(modular, G),
+            "outputs_equal_value": modular["same"]}
+    # (where both forms run on one kernel, their own kernels are what differs)
+    line["forms_bit_identical"] = bool(
+        forms_agree and all(x["same"] for x in (gemm, modular) if x))
     if oracle_rows:
         line["outputs_equal_oracle"] = {
             f: (None if v is None else f"{v}/{G} rows")
