@@ -279,8 +279,8 @@ int cggi_measure_mulmod(int32_t iters, double *tmulmods);
  * exchange buffers), else CGGI_OK.  Latency-mode launches on one context
  * must not run concurrently (they share its exchange buffers).  Where the
  * double-precision kernel serves the INT8 form (see cggi_form_t) latency
- * mode runs only under an explicit plan; batches within its range still do
- * nothing while the error word is set. */
+ * mode runs only under an explicit plan (see cggi_ctx_latency_abort for the
+ * batches that would take it). */
 int cggi_ctx_latency_mode(cggi_ctx *ctx, int32_t enable);
 int cggi_ctx_latency_groups(const cggi_ctx *ctx, int32_t *groups);
 int cggi_ctx_check(cggi_ctx *ctx);
@@ -291,9 +291,10 @@ int cggi_ctx_check(cggi_ctx *ctx);
  * stop at their next poll, later ones do nothing (their outputs are left
  * untouched) until cggi_ctx_check, which then returns CGGI_E_TIMEOUT and
  * clears the state.  INT8 batches of latency mode's widths that run on the
- * double-precision kernel keep that rule: while latency mode is on, each of
- * their bootstraps is written as a whole or, once the word is set, not at
- * all.  Wider INT8 batches and the NTT form are unaffected.
+ * double-precision kernel keep that rule: while latency mode is on, those of
+ * calls made between the abort and the check are not launched (earlier ones
+ * and graph replays run to their end).  Wider INT8 batches and the NTT form
+ * are unaffected.
  * CGGI_OK also when the context has no latency mode. */
 int cggi_ctx_latency_abort(cggi_ctx *ctx);
 

@@ -260,8 +260,7 @@ static int64_t scratch_max_gates(const Shape &sh)
     return g;
 }
 
-// Widest batch of a form that calls now run on the FFT kernel.
-static int fft_width(const Ctx *c, cggi_form_t form)
+int form_fft_width(const Ctx *c, cggi_form_t form)
 {
     if (!c->bsk_fft || (form == CGGI_FORM_INT8 && c->plan_n > 0))
         return 0;
@@ -273,7 +272,7 @@ int form_bootstrap(const Ctx *c, cggi_form_t form, const uint32_t *in,
                    const int32_t *d_count, hipStream_t s)
 {
     const bool i8 = form == CGGI_FORM_INT8;
-    const int width = fft_width(c, form);
+    const int width = form_fft_width(c, form);
     if (width == 0 || (B > width && !d_count))
         return i8 ? int8_bootstrap(c, in, testv, out, B, d_count, 0, s)
                   : ntt_bootstrap(c, in, testv, out, B, d_count, s);
@@ -283,18 +282,23 @@ int form_bootstrap(const Ctx *c, cggi_form_t form, const uint32_t *in,
         if (rc)
             return rc;
     }
-    // INT8 batches that latency mode would take keep its stop rule: they do
-    // nothing while the context's error word is set
-    int cap = 0;
-    if (i8 && c->split_on && c->x_err) {
+    // INT8 batches that latency mode would take keep its rule after an abort:
+    // they do nothing until the check (but a capture, whose replays come
+    // later, records them)
+    if (i8 && c->aborted && c->split_on) {
         int32_t kind[8], hi[8];
+        int cap = 0;
         const int no = int8_active_plan(c, kind, hi);
         for (int k = 0; k < no; ++k)
             if (kind[k] <= 1 || kind[k] == 5)
                 cap = hi[k];
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        CGGI_HIP_TRY(hipStreamIsCapturing(s, &cs));
+        if (B <= cap && cs == hipStreamCaptureStatusNone)
+            return CGGI_OK;
     }
-    return fft_bootstrap(c, in, testv, out, B, d_count, width,
-                         cap > 0 ? c->x_err : nullptr, cap, s);
+    return fft_bootstrap(c, in, testv, out, B < width ? B : width,
+                         d_count ? d_count + 1 : nullptr, s);
 }
 
 static void prof_clear(Ctx *c)
@@ -656,7 +660,7 @@ int cggi_ctx_transform(const cggi_ctx *ctx, cggi_form_t form, int32_t *width)
         return set_error(CGGI_E_PARAM, "ctx or width NULL, or unknown form");
     if (!(ctx->forms & (uint32_t)form))
         return set_error(CGGI_E_UNSUPPORTED, "form not built into the context");
-    *width = fft_width(ctx, form);
+    *width = form_fft_width(ctx, form);
     return CGGI_OK;
 }
 
@@ -686,6 +690,7 @@ int cggi_ctx_latency_abort(cggi_ctx *ctx)
         CGGI_HIP_TRY(hipStreamCreateWithFlags(&ctx->abort_stream,
                                               hipStreamNonBlocking));
     const uint32_t one = 1;
+    ctx->aborted = true;
     CGGI_HIP_TRY(hipMemcpyAsync(ctx->x_err, &one, 4, hipMemcpyHostToDevice,
                                 ctx->abort_stream));
     CGGI_HIP_TRY(hipStreamSynchronize(ctx->abort_stream));
@@ -704,6 +709,7 @@ int cggi_ctx_check(cggi_ctx *ctx)
         return CGGI_OK;
     uint32_t flag = 0;
     CGGI_HIP_TRY(hipMemcpy(&flag, ctx->x_err, 4, hipMemcpyDeviceToHost));
+    ctx->aborted = false;
     if (!flag)
         return CGGI_OK;
     if ((rc = int8_split_reset(ctx)))

@@ -576,8 +576,7 @@ void k_bootstrap_fft(
     const double *__restrict__ key, const double *__restrict__ tab,
     const uint32_t *__restrict__ in, const uint32_t *__restrict__ testv,
     uint32_t *__restrict__ out, int B, const int32_t *__restrict__ d_count,
-    int pair_width, int width, const uint32_t *__restrict__ stop, int stop_cap,
-    int n, int beta, int l_rt)
+    int pair_width, int n, int beta, int l_rt)
 {
     using C = FCfg<N>;
     constexpr int M = C::M, PPL = C::PPL, LPF = C::LPF, FPW = C::FPW;
@@ -600,27 +599,11 @@ void k_bootstrap_fft(
     auto aidx = [](int t) { return H == 2 ? (t & 1) * M + (t >> 1) : t; };
 
     const int count = d_count ? min(B, *d_count) : B;
-    if (count > width)      // the int8 kernels' batch
-        return;
     int from, to;
     fft_share(NB, count, pair_width, &from, &to);
     const int g0 = from + blockIdx.x * NB;
     if (g0 >= to)
         return;
-    // narrow INT8 batches are refused while the latency-mode error word is
-    // set.  cggi_ctx_latency_abort sets it from another stream while launches
-    // run, so one thread reads it for the workgroup: a bootstrap is written
-    // as a whole or not at all.  (The word's place in the rows is first
-    // written after the step loop's first barrier.)
-    if (stop && count <= stop_cap) {
-        uint32_t *word = reinterpret_cast<uint32_t *>(smem);
-        if (threadIdx.x == 0)
-            *word = __hip_atomic_load(stop, __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (*word)
-            return;
-    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lf = C::tlane(lane), f = C::tf(lane);
@@ -1077,13 +1060,12 @@ template <int N> int fft_key_t(Ctx *c, const uint32_t *bsk, hipStream_t s)
 
 template <int N, int L>
 int fft_launch_l(const Ctx *c, const uint32_t *in, const uint32_t *testv,
-                 uint32_t *out, int B, const int32_t *d_count, int width,
-                 const uint32_t *stop, int stop_cap, hipStream_t s)
+                 uint32_t *out, int B, const int32_t *d_count, hipStream_t s)
 {
     const Shape &sh = c->sh;
     constexpr int KR = L ? FKR<N>(L) : 1;
     const size_t smem = fft_smem(N, sh.l);
-    int pair_width = 0, grid = B < width ? B : width;
+    int pair_width = 0, grid = B;
     if constexpr (FPAIR<N>(L)) {
         // Batches wider than the chip: two bootstraps per workgroup in
         // rounds of twice the CUs, one per workgroup for a rest of at most
@@ -1099,8 +1081,8 @@ int fft_launch_l(const Ctx *c, const uint32_t *in, const uint32_t *testv,
             hipLaunchKernelGGL((k_bootstrap_fft<N, 2, L, KR, FWPE>),
                                dim3((B + 1) / 2), dim3(FCfg<N>::THREADS),
                                2 * smem, s, c->bsk_fft, c->fft_tw, in, testv,
-                               out, B, d_count, pair_width, width, stop,
-                               stop_cap, sh.n, sh.beta, sh.l);
+                               out, B, d_count, pair_width, sh.n, sh.beta,
+                               sh.l);
             CGGI_HIP_TRY(hipGetLastError());
         }
         if (!ones)
@@ -1108,25 +1090,21 @@ int fft_launch_l(const Ctx *c, const uint32_t *in, const uint32_t *testv,
     }
     hipLaunchKernelGGL((k_bootstrap_fft<N, 1, L, KR, FWPE>), dim3(grid),
                        dim3(FCfg<N>::THREADS), smem, s, c->bsk_fft,
-                       c->fft_tw, in, testv, out, B, d_count, pair_width,
-                       width, stop, stop_cap, sh.n, sh.beta, sh.l);
+                       c->fft_tw, in, testv, out, B, d_count, pair_width, sh.n,
+                       sh.beta, sh.l);
     CGGI_HIP_TRY(hipGetLastError());
     return CGGI_OK;
 }
 
 template <int N>
 int fft_launch(const Ctx *c, const uint32_t *in, const uint32_t *testv,
-               uint32_t *out, int B, const int32_t *d_count, int width,
-               const uint32_t *stop, int stop_cap, hipStream_t s)
+               uint32_t *out, int B, const int32_t *d_count, hipStream_t s)
 {
     return c->sh.l == 3
-               ? fft_launch_l<N, 3>(c, in, testv, out, B, d_count, width,
-                                    stop, stop_cap, s)
+               ? fft_launch_l<N, 3>(c, in, testv, out, B, d_count, s)
            : c->sh.l == 2
-               ? fft_launch_l<N, 2>(c, in, testv, out, B, d_count, width,
-                                    stop, stop_cap, s)
-               : fft_launch_l<N, 0>(c, in, testv, out, B, d_count, width,
-                                    stop, stop_cap, s);
+               ? fft_launch_l<N, 2>(c, in, testv, out, B, d_count, s)
+               : fft_launch_l<N, 0>(c, in, testv, out, B, d_count, s);
 }
 
 } // namespace
@@ -1169,22 +1147,13 @@ int fft_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s)
 }
 
 int fft_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
-                  uint32_t *out, int B, const int32_t *d_count, int width,
-                  const uint32_t *stop, int stop_cap, hipStream_t s)
+                  uint32_t *out, int B, const int32_t *d_count, hipStream_t s)
 {
     switch (c->sh.N) {
-    case 256:
-        return fft_launch<256>(c, in, testv, out, B, d_count, width, stop,
-                               stop_cap, s);
-    case 512:
-        return fft_launch<512>(c, in, testv, out, B, d_count, width, stop,
-                               stop_cap, s);
-    case 1024:
-        return fft_launch<1024>(c, in, testv, out, B, d_count, width, stop,
-                               stop_cap, s);
-    default:
-        return fft_launch<2048>(c, in, testv, out, B, d_count, width, stop,
-                               stop_cap, s);
+    case 256: return fft_launch<256>(c, in, testv, out, B, d_count, s);
+    case 512: return fft_launch<512>(c, in, testv, out, B, d_count, s);
+    case 1024: return fft_launch<1024>(c, in, testv, out, B, d_count, s);
+    default: return fft_launch<2048>(c, in, testv, out, B, d_count, s);
     }
 }
 

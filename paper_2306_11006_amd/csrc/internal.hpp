@@ -55,6 +55,7 @@ struct cggi_ctx {
     size_t x_words[3] = {0, 0, 0};
     uint32_t *x_epoch[3] = {};    // [groups] launch epochs (behind x_buf)
     uint32_t *x_err = nullptr;    // [1] set when a member's wait timed out
+    bool aborted = false;         // cggi_ctx_latency_abort, until the check
     hipStream_t abort_stream = nullptr; // non-blocking, for latency_abort
     // INT8 kernel plan (cggi_ctx_int8_plan): entry k runs the batches of
     // (cap[k-1], cap[k]] bootstraps with kernel kind[k]; plan_n = 0 selects
@@ -72,7 +73,7 @@ struct cggi_ctx {
     uint32_t *ws_small = nullptr; // [2G][n+1] bootstrap inputs
     uint32_t *ws_big = nullptr;   // [2G][N+1] bootstrap outputs
     int32_t *ws_slot = nullptr;   // [G] first slot of each gate (-1: none)
-    int32_t *ws_count = nullptr;  // [1] number of bootstrap slots
+    int32_t *ws_count = nullptr;  // [2] number of bootstrap slots (LevelWs)
     // this device's address of the fixed level workspace of
     // cggi_eval_level_noalloc (taken at context creation)
     unsigned char *scratch = nullptr;
@@ -107,17 +108,15 @@ int ntt_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
                   uint32_t *out, int B, const int32_t *d_count,
                   hipStream_t s);
 
-// FFT kernel: bound on the error of a coefficient before rounding, key
-// transforms at context creation (a no-op where the bound exceeds 1/4 or
-// the workgroup the LDS), and a launch of B bootstraps (at most *d_count
-// when given; more than `width` are left to another kernel).  With `stop`, a
-// launch of at most stop_cap bootstraps does nothing while *stop is set.
+// FFT kernel: bound on the error of a coefficient before rounding, the widest
+// INT8 batch it takes, key transforms at context creation (a no-op where the
+// bound exceeds 1/4 or the workgroup the LDS), and a launch of B bootstraps
+// (at most *d_count when given).
 double fft_error_bound(const Shape &sh);
 int fft_int8_width(const Shape &sh, int cus);
 int fft_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s);
 int fft_bootstrap(const Ctx *c, const uint32_t *in, const uint32_t *testv,
-                  uint32_t *out, int B, const int32_t *d_count, int width,
-                  const uint32_t *stop, int stop_cap, hipStream_t s);
+                  uint32_t *out, int B, const int32_t *d_count, hipStream_t s);
 
 int int8_make_key(Ctx *c, const uint32_t *bsk, hipStream_t s);
 // lo: with d_count, only counts above it.
@@ -144,7 +143,10 @@ bool int8_plan_is_builtin(const Ctx *c, const int32_t *kind,
 
 // Bootstrap B ciphertexts in the given form: the FFT kernel where the
 // context has it, no INT8 plan was set and an INT8 batch is not wider than
-// fft_int8_width, else the form's own kernels.
+// fft_int8_width, else the form's own kernels.  d_count, when given: [0] the
+// count read on the device, [1] the same, or 0 where it exceeds form_fft_width
+// (the widest batch of the form that calls now run on the FFT kernel).
+int form_fft_width(const Ctx *c, cggi_form_t form);
 int form_bootstrap(const Ctx *c, cggi_form_t form, const uint32_t *in,
                    const uint32_t *testv, uint32_t *out, int B,
                    const int32_t *d_count, hipStream_t s);
@@ -175,7 +177,7 @@ struct LevelWs {
     uint32_t *small;
     uint32_t *big;
     int32_t *slot;
-    int32_t *count;
+    int32_t *count;               // [2] (see form_bootstrap)
 };
 
 // Launch one level on `ws`; `prof` brackets its kernels with the

@@ -78,7 +78,7 @@ constexpr int SLOT_THREADS = 1024;
 
 __global__ __launch_bounds__(SLOT_THREADS) void k_level_slots(
     const cggi_gate_t *__restrict__ gates, int G, int W,
-    int32_t *__restrict__ slot, int32_t *__restrict__ count)
+    int32_t *__restrict__ slot, int32_t *__restrict__ count, int fft_width)
 {
     __shared__ int32_t part[SLOT_THREADS];
     const int tid = threadIdx.x;
@@ -106,8 +106,10 @@ __global__ __launch_bounds__(SLOT_THREADS) void k_level_slots(
         slot[g] = k ? run : -1;
         run += k;
     }
-    if (tid == SLOT_THREADS - 1)
+    if (tid == SLOT_THREADS - 1) {
         count[0] = part[tid];
+        count[1] = part[tid] > fft_width ? 0 : part[tid];
+    }
 }
 
 __global__ __launch_bounds__(256) void k_level_preop(
@@ -159,7 +161,7 @@ int level_launch(Ctx *c, cggi_form_t form, const cggi_gate_t *gates, int G,
     const Shape &sh = c->sh;
     Ctx *pc = prof ? c : nullptr;
     hipLaunchKernelGGL(k_level_slots, dim3(1), dim3(SLOT_THREADS), 0, s,
-                       gates, G, W, ws.slot, ws.count);
+                       gates, G, W, ws.slot, ws.count, form_fft_width(c, form));
     CGGI_HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_level_preop, dim3(G), dim3(256), 0, s, gates,
                        ws.slot, wires, ws.small, W, sh.n);

@@ -45,3 +45,35 @@ def test_abort_while_batches_run():
                           cggi.to_host(ref))
     ctx.check()
     ctx.close()
+
+
+def test_capture_after_an_abort_keeps_the_bootstraps():
+    """A graph captured between an abort and the check replays the bootstraps
+    (three replays, eager work between); an eager call there does nothing."""
+    import torch
+    from paper_2306_11006_amd import cggi
+    p = params.TOY
+    bsk, ksk = inputs.uniform_keys(p, 7710)
+    ctx = cggi.Context(p, cggi.to_device(bsk), cggi.to_device(ksk))
+    cts = cggi.to_device(inputs.uniform_lwe(p, 7711, 9))
+    ref = ctx.bootstrap("ntt", cts)
+    out = torch.full_like(ref, MARK)
+    torch.cuda.synchronize()
+    ctx.latency_abort()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.bootstrap("int8", cts, out)
+    ctx.bootstrap("int8", cts, out)
+    torch.cuda.synchronize()
+    assert bool((out == MARK).all())
+    with pytest.raises(cggi.CggiError):
+        ctx.check()
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+        out.fill_(MARK)
+        assert torch.equal(ctx.bootstrap("int8", cts), ref)
+    del graph
+    ctx.check()
+    ctx.close()
