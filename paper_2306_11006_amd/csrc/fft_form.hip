@@ -618,7 +618,9 @@ void k_bootstrap_fft(
     for (int b = 0; b < NB; ++b) {
         const int e = (2 * N - (int)fft_modswitch(ct[b][n], LOG2_2N)) &
                       (2 * N - 1);
-        for (int m = tid; m < N; m += T) {
+#pragma unroll
+        for (int q = 0; q < N / T; ++q) {
+            const int m = tid + q * T;
             uint32_t v = testv ? testv[m] : (1u << 29);
             int t = m + e;
             if (t >= 2 * N) {
