@@ -50,9 +50,10 @@ typedef struct {
 
 /* Forms of the negacyclic products inside the blind rotation.  Both give
  * bit-identical results.  Where a double-precision transform is proven to
- * round to the exact integers (csrc/fft_form.hip; Bg up to 2^13 or so, every
- * parameter set of params.py), both forms run on that kernel; a context then
- * keeps the key's transforms (64 * n*2l*N bytes) instead of the NTT form's.
+ * round to the exact integers (csrc/fft_form.hip, fft_error_bound: at l = 2 for
+ * Bg up to 2^15, 2^14, 2^13 and 2^11 at N = 256 to 2048; every parameter set of
+ * params.py), both forms run on that kernel; a context then keeps the key's
+ * transforms (32 * n*2l*N bytes) instead of the NTT form's.
  * The kernels below serve the other parameter sets and, for INT8, an explicit
  * kernel plan (cggi_ctx_int8_plan) and the widths where they are faster (wide
  * batches at N <= 512 and Bg <= 2^7; cggi_ctx_transform tells).
@@ -98,7 +99,7 @@ int cggi_params_check(const cggi_params_t *params);
 /* Create a context on the current HIP device.  Reads d_bsk
  * ([n][2l][2][N]) once to derive the key forms selected by `forms` (a
  * bitmask of cggi_form_t): the key's double-precision transforms where they
- * serve (64 * n*2l*N bytes; see cggi_form_t), else for the NTT form the
+ * serve (32 * n*2l*N bytes; see cggi_form_t), else for the NTT form the
  * bootstrapping key transformed mod Q (8 * n*2l*2*N bytes); the INT8 form
  * stores its int8 limb windows (n*R*2*4*(N+64) bytes, R = 2l digit rows for Bg <= 2^7,
  * 4l for Bg <= 2^13) and, for N <= 1024, the key-only correction of its

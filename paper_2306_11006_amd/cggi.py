@@ -254,8 +254,9 @@ class Context:
         return bm.value, bn.value, km.value, kn.value
 
     def latency_mode(self, enable=True):
-        """Turn the INT8 form's latency mode (narrow batches over four CUs
-        per column tile) on or off."""
+        """Turn the INT8 form's latency mode (narrow batches over eight, four
+        or two CUs per column tile) on or off; it runs under an explicit plan
+        and where the double-precision kernel does not serve."""
         _check(lib().cggi_ctx_latency_mode(self._h, int(bool(enable))))
 
     def latency_groups(self):

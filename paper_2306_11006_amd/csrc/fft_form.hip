@@ -45,7 +45,7 @@
 // write; an unswizzled one 360).
 //
 // What bounds it: at N = 1024 a step takes 8,300 cycles for one bootstrap and
-// 15,300 for two.  The VALU issues 3,800 wave instructions of it per bootstrap
+// 15,300 for two.  The VALU issues 3,798 wave instructions of it per bootstrap
 // (3,100 are the transforms' and sums' f64 work, 4.4 to 5.1 cycles each on a
 // SIMD), the LDS is active 3,460 cycles, and the key's 192 KB come through the
 // CU's vector cache at 64 bytes a cycle behind them; since the waves leave a

@@ -21,8 +21,8 @@
 // GEMM on v_mfma_i32_32x32x32_i8 (k_ks_mfma): with the one-hot digit matrix
 // A[g][(j, p, h)] = (d_{g,j,p} == h) and the key as four signed int8 limbs,
 // sum_{j,p} ksk[j][p][d_{g,j,p}][c] = sum_k A[g][k] * ksk[k][c].  The key
-// (tens of MB) is then streamed once per 128 ciphertexts instead of being
-// gathered row by row for every ciphertext.
+// (tens of MB) is then streamed once per 32 RT ciphertexts (RT = 2 or 4) instead
+// of being gathered row by row for every ciphertext.
 #include "internal.hpp"
 
 #include <algorithm>
